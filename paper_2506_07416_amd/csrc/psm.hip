@@ -5,222 +5,558 @@
 // selection fuses with its lexical scores.
 //
 // The module is tiny (d = 256, 4 layers, 128 tokens at the benchmark shape),
-// so every step is latency-bound: the kernels favour few launches and few
-// dependent global round trips over peak rates.
-//   - psm_gemm_kernel: bf16 MFMA (v_mfma_f32_32x32x16_bf16) on A [M, K] times
-//     W^T, W [N, K] fp32 from the parameter vector (rounded to bf16 as it is
-//     loaded). A workgroup owns one 32 x 32 output block and splits the k range
-//     over its 4 waves (more workgroups, fewer round trips each); A is either
-//     bf16 or the LayerNorm of fp32 rows formed as the operands load (the norm
-//     needs no launch of its own). Epilogues: bias plus a split bf16 output
-//     (Q/K/V), GELU, or an add into the fp32 residual stream.
+// so a forward is a chain of short launches: what a launch costs is its
+// dependent round trips to memory, not its arithmetic, and beyond a few
+// hundred rows the cache traffic of its tiles.
+//   - psm_gemm_kernel: bf16 MFMA (v_mfma_f32_16x16x32_bf16) on A [M, K] times
+//     W^T, W [N, K] fp32 from the parameter vector. A workgroup asks for its
+//     whole first tile at once in whole rows, rounds it to bf16 on the way to
+//     LDS and multiplies from there; A is bf16 or the LayerNorm of fp32 rows.
 //   - self-attention: the library's prefill attention kernel, non-causal.
-//   - psm_cross_kernel: per (view, sample): the latent's query, its softmax over
-//     the encoded tokens, the attended value and the view's head.
+//   - psm_head_kernel: the cross-attention and the heads (7 us for one query;
+//     forming the K and V rows and attending to them took 16 + 18.6 us). The latent side is
+//     folded first, by a few workgroups beside the first layer's GEMMs
+//     (psm_fold): with q_v = W_cq lat_v + b_cq, a token's logit is
+//     x_t . (W_ck^T q_v) and its share of the view's output x_t . (W_cv^T w_v)
+//     (w_v the head's weights), each plus a constant, so no K or V rows are
+//     ever formed.
 #include "common.hpp"
 #include "launch.hpp"
 
 namespace litevlm {
 namespace {
 
+typedef uint32_t psm_u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t psm_u32x4 __attribute__((ext_vector_type(4)));
 
-__device__ __forceinline__ int psm_acc_row(int r, int hl) { return 8 * (r >> 2) + 4 * hl + (r & 3); }
+// Exact-erf GELU, x * erfc(-x/sqrt(2)) / 2, branch-free: with z = |x|/sqrt(2) and
+// t = 1/(1 + 0.4 z), erfc(z) = t exp(-z^2) P(t), P of degree 8 fitted to
+// erfc(z) exp(z^2) / t over all z >= 0 (least squares reweighted towards equal
+// relative error: 1.3e-7). Negative x needs no cancelling 1 + erf: the absolute
+// error is 3.9e-7 at most, that of 0.5 x (1 + erf) in fp32 4.5e-7.
+__device__ __forceinline__ float gelu_erf(float x) {
+  const float z = fabsf(x) * 0.7071067811865476f;
+  const float t = __builtin_amdgcn_rcpf(fmaf(0.4f, z, 1.f));
+  float P = 0.050258949398994446f;
+  P = fmaf(P, t, -0.18288986384868622f);
+  P = fmaf(P, t, 0.16906839609146118f);
+  P = fmaf(P, t, -0.005594694521278143f);
+  P = fmaf(P, t, 0.14142614603042603f);
+  P = fmaf(P, t, 0.16854313015937805f);
+  P = fmaf(P, t, 0.20784257352352142f);
+  P = fmaf(P, t, 0.22566960752010345f);
+  P = fmaf(P, t, 0.22567586600780487f);
+  const float e = 0.5f * t * P * __builtin_amdgcn_exp2f(-z * z * kLog2e);  // erfc(z) / 2
+  return x * (x > 0.f ? 1.f - e : e);
+}
 
-__device__ __forceinline__ float gelu_erf(float x) { return 0.5f * x * (1.f + erff(x * 0.7071067811865476f)); }
+// Two fp32 values to packed bf16 (round to nearest even).
+__device__ __forceinline__ uint32_t psm_pk(float lo, float hi) {
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  return __builtin_bit_cast(uint32_t, bf16x2{(__bf16)lo, (__bf16)hi});
+}
 
 enum { kOutBf16 = 0, kOutGelu = 1, kOutResid = 2 };
 
-// out = A W^T + bias for one 32 x 32 output block per workgroup, the k range
-// split over its 4 waves (wave w: columns [w*K/4, (w+1)*K/4)) and the partial
-// blocks summed through LDS in wave order. A is either bf16 x [M, K] or, with
-// LNIN, the LayerNorm of the fp32 rows src [M, K] (gain g, bias bt, eps 1e-5),
-// formed as the operands load; every wave first takes the mean and variance of
-// the block's 32 rows (lane l32 / half hl: half hl of row l32).
-// Output: kOutBf16 columns split into nsplit equal ranges, range j to out[j]
-// [M, N/nsplit]; kOutGelu bf16 gelu(.) to out[0] [M, N]; kOutResid
-// h [M, N] = (rsrc ? rsrc : h) + (.). The block at (0, 0) also writes the
-// per-sample row offsets cu[t] = t*T (t <= B) when cu is given.
-template <int MODE, bool LNIN>
-__global__ __launch_bounds__(256) void psm_gemm_kernel(const uint16_t* __restrict__ x, const float* __restrict__ src,
-                                                       const float* __restrict__ g, const float* __restrict__ bt,
-                                                       const float* __restrict__ W, const float* __restrict__ bias,
-                                                       int M, int N, int K, uint16_t* out0, uint16_t* out1,
-                                                       uint16_t* out2, int nsplit, float* h,
-                                                       const float* __restrict__ rsrc, int32_t* cu, int B, int T) {
-  __shared__ float red[4][16][kWave];
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int l32 = lane & 31, hl = lane >> 5;
-  const int m0 = blockIdx.x * 32, n0 = blockIdx.y * 32;
-  if (cu && blockIdx.x == 0 && blockIdx.y == 0)
-    for (int t = threadIdx.x; t <= B; t += 256) cu[t] = t * T;
-  const int arow = min(m0 + l32, M - 1);
-  float mu = 0.f, rstd = 1.f;
-  if constexpr (LNIN) {
-    const float4* rp = reinterpret_cast<const float4*>(src + (size_t)arow * K) + hl * (K / 8);
-    float s1 = 0.f, s2 = 0.f;
-#pragma unroll 8
-    for (int i = 0; i < K / 8; ++i) {
-      const float4 v = rp[i];
-      s1 += (v.x + v.y) + (v.z + v.w);
-      s2 = fmaf(v.x, v.x, fmaf(v.y, v.y, fmaf(v.z, v.z, fmaf(v.w, v.w, s2))));
+// The latent side of the cross-attention, folded by the workgroups past the
+// GEMM's own: stage 1 forms q_v, g_v = W_cv^T w_v and cst_v = w_v . b_cv +
+// b_head_v, stage 2 (a later launch) u_v = W_ck^T q_v. All fp32.
+struct PsmFold {
+  int stage, d, n_views;  // stage 0: nothing
+  const float *lat, *w_cq, *b_cq, *w_ck, *w_cv, *b_cv, *w_hd, *b_hd;
+  float *qv, *u, *g, *cst;  // [N, d], [N, d], [N, d], [N]
+};
+
+// Workgroups of a stage: q_v takes four rows of W_cq each, the column sums 32 columns each.
+__host__ __device__ constexpr int psm_fold_blocks(int stage, int d) {
+  return stage == 0 ? 0 : (stage == 1 ? d / 4 + d / 32 : d / 32);
+}
+constexpr int kFoldViews = 8;  // views of one pass
+constexpr int kFoldLds = (kFoldViews * 512 + 4 * kFoldViews * 32) * 4;
+
+__device__ __forceinline__ float psm_wave_sum(float x) { return sum_xor32(sum_xor16(row16_sum(x))); }
+
+// out[v][c] = sum_j w[v][j] W[j][c] for 32 columns c: thread (float4 piece tid
+// % 8 of the columns, rows j = tid/8 mod 32), its W pieces all requested at
+// once, the views' w rows in LDS; sums over the wave's eight row groups by
+// lane exchanges, over the waves through LDS in wave order.
+template <int D>
+__device__ void psm_fold_cols(const float* __restrict__ W, const float* __restrict__ w, float* __restrict__ out, int c0,
+                              int n_views, float* lds) {
+  constexpr int NJ = D / 32;
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, c4 = tid & 7, jg = tid >> 3;
+  float* red = lds + kFoldViews * 512;
+  float4 x[NJ];
+#pragma unroll
+  for (int i = 0; i < NJ; ++i) x[i] = *reinterpret_cast<const float4*>(W + (size_t)(jg + 32 * i) * D + c0 + 4 * c4);
+  for (int v0 = 0; v0 < n_views; v0 += kFoldViews) {
+    const int nv = min(kFoldViews, n_views - v0);
+    for (int i = tid; i < nv * D; i += 256) lds[i] = w[(size_t)v0 * D + i];
+    __syncthreads();
+    for (int v = 0; v < nv; ++v) {
+      float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+      for (int i = 0; i < NJ; ++i) {
+        const float f = lds[v * D + jg + 32 * i];
+        s = make_float4(fmaf(f, x[i].x, s.x), fmaf(f, x[i].y, s.y), fmaf(f, x[i].z, s.z), fmaf(f, x[i].w, s.w));
+      }
+      s = make_float4(s.x + dpp<0x128>(s.x), s.y + dpp<0x128>(s.y), s.z + dpp<0x128>(s.z), s.w + dpp<0x128>(s.w));  // row_ror:8
+      s = make_float4(sum_xor32(sum_xor16(s.x)), sum_xor32(sum_xor16(s.y)), sum_xor32(sum_xor16(s.z)),
+                      sum_xor32(sum_xor16(s.w)));
+      if (lane < 8) *reinterpret_cast<float4*>(red + (v * 4 + wv) * 32 + 4 * c4) = s;
     }
-    s1 = sum_xor32(s1);
-    s2 = sum_xor32(s2);
-    mu = s1 / K;
-    rstd = 1.f / sqrtf(fmaxf(s2 / K - mu * mu, 0.f) + 1e-5f);
+    __syncthreads();
+    if (tid < 32 * nv) {
+      const int v = tid >> 5, c = tid & 31;
+      out[(size_t)(v0 + v) * D + c0 + c] =
+          ((red[v * 128 + c] + red[v * 128 + 32 + c]) + red[v * 128 + 64 + c]) + red[v * 128 + 96 + c];
+    }
+    __syncthreads();
   }
-  const int kw = K / 4, kbeg = w * kw;
-  const float* bp = W + (size_t)(n0 + l32) * K + kbeg + 8 * hl;
-  auto a_op = [&](int k) __attribute__((always_inline)) {
-    if constexpr (LNIN) {
-      const int c = kbeg + k + 8 * hl;
-      const float* xr = src + (size_t)arow * K + c;
-      const float4 x0 = *reinterpret_cast<const float4*>(xr), x1 = *reinterpret_cast<const float4*>(xr + 4);
-      const float4 g0 = *reinterpret_cast<const float4*>(g + c), g1 = *reinterpret_cast<const float4*>(g + c + 4);
-      const float4 b0 = *reinterpret_cast<const float4*>(bt + c), b1 = *reinterpret_cast<const float4*>(bt + c + 4);
-      const float y[8] = {(x0.x - mu) * rstd * g0.x + b0.x, (x0.y - mu) * rstd * g0.y + b0.y,
-                          (x0.z - mu) * rstd * g0.z + b0.z, (x0.w - mu) * rstd * g0.w + b0.w,
-                          (x1.x - mu) * rstd * g1.x + b1.x, (x1.y - mu) * rstd * g1.y + b1.y,
-                          (x1.z - mu) * rstd * g1.z + b1.z, (x1.w - mu) * rstd * g1.w + b1.w};
-      return pack_bf16x8(y);
-    } else {
-      return __builtin_bit_cast(bf16x8, *reinterpret_cast<const psm_u32x4*>(x + (size_t)arow * K + kbeg + k + 8 * hl));
+}
+
+template <int D>
+__device__ void psm_fold(const PsmFold& f, int blk, float* lds) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  if (f.stage == 2) {
+    psm_fold_cols<D>(f.w_ck, f.qv, f.u, 32 * blk, f.n_views, lds);
+    return;
+  }
+  if (blk >= D / 4) {
+    psm_fold_cols<D>(f.w_cv, f.w_hd, f.g, 32 * (blk - D / 4), f.n_views, lds);
+    return;
+  }
+  // q_v[j] for row j = 4*blk + w of W_cq
+  constexpr int P = D / 256;  // float4 pieces per lane
+  const int j = 4 * blk + w;
+  float4 x[P];
+#pragma unroll
+  for (int i = 0; i < P; ++i) x[i] = reinterpret_cast<const float4*>(f.w_cq + (size_t)j * D)[lane + 64 * i];
+  for (int v0 = 0; v0 < f.n_views; v0 += 8) {  // eight latents in flight
+    float s[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const float4* l4 = reinterpret_cast<const float4*>(f.lat + (size_t)min(v0 + e, f.n_views - 1) * D) + lane;
+      s[e] = 0.f;
+#pragma unroll
+      for (int i = 0; i < P; ++i) {
+        const float4 l = l4[64 * i];
+        s[e] = fmaf(x[i].x, l.x, fmaf(x[i].y, l.y, fmaf(x[i].z, l.z, fmaf(x[i].w, l.w, s[e]))));
+      }
+    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const float t = psm_wave_sum(s[e]);
+      if (lane == 0 && v0 + e < f.n_views) f.qv[(size_t)(v0 + e) * D + j] = t + f.b_cq[j];
+    }
+  }
+  // cst_v: view v by wave v % 4 of workgroup v / 4 (of at most 16)
+  const int v = 4 * blk + w;
+  if (v < f.n_views) {
+    float s = 0.f;
+#pragma unroll
+    for (int i = 0; i < D / 64; ++i) s = fmaf(f.w_hd[(size_t)v * D + lane + 64 * i], f.b_cv[lane + 64 * i], s);
+    s = psm_wave_sum(s);
+    if (lane == 0) f.cst[v] = s + f.b_hd[v];
+  }
+}
+
+struct PsmGemm {
+  const uint16_t* x;   // bf16 A [M, K], or
+  const float* src;    // fp32 rows [M, K] to be normalised with gain g, bias bt
+  const float *g, *bt;
+  const float *W, *bias;  // [N, K], [N]
+  int M, N, K;
+  uint16_t *o0, *o1, *o2;  // bf16 outputs
+  float* h;                // fp32 residual stream
+  const float* rsrc;       // what the residual is added to (may be h itself)
+  int32_t* cu;             // row offsets to write (first launch), or NULL
+  int B, T;
+  int mt, nt, per_xcd;     // tiles, and items per XCD
+  PsmFold fold;
+};
+
+// out = A W^T + bias for one BM x BN output tile per workgroup: NW waves as 2 x
+// NW/2, each its share of the tile in 16 x 16 MFMA blocks. KG = 2: two such wave
+// groups take alternate chunks of the k range, their sums added through LDS.
+//
+// Bound by latency at a few hundred rows: one query (128 rows, d 256) takes 4.5
+// to 6.5 us a launch, of which the arithmetic is under 0.1 us. What this form
+// replaced read operands of 32 rows x 32 bytes an instruction in four dependent
+// steps, the norm's statistics before them (QKV 9.3 us, up 9.9 us; batch 8:
+// 21 and 32 us).
+//
+// LND = 0: A is bf16 x [M, K], staged in chunks beside W's. LND = d = K: A is
+// the LayerNorm (eps 1e-5) of the fp32 rows src, formed once into an LDS panel
+// of whole rows; 16 lanes hold a row in registers, so the mean and the squared
+// deviations are two register passes. A chunk is 8192 values of W (KC columns,
+// 32 KB fp32): each thread asks for 128 bytes of it in 16-byte pieces, whole
+// rows to a wave, two chunks ahead of use. The chunk is rounded to bf16 into
+// LDS rows whose 16-byte pieces are XOR-swizzled, so that the operand reads
+// (16 rows x 1 piece) are conflict-free.
+//
+// The products are formed transposed (W rows as the A operand), so a lane ends
+// with four consecutive output columns of one row.
+//
+// Modes: kOutBf16 to o0, o1, o2 (equal thirds of N); kOutGelu bf16 gelu(.) to
+// o0; kOutResid h = rsrc + (.).
+template <int MODE, int LND, int BM, int BN, int NW, int KG>
+__global__ __launch_bounds__(64 * NW * KG, 2) void psm_gemm_kernel(PsmGemm p) {
+  constexpr int KC = 8192 / BN;                 // columns per chunk
+  constexpr int NPW = KC / 8;                   // 16-byte pieces per staged W (and bf16 A) row
+  constexpr int ARB = LND ? 2 * LND : 2 * KC;   // bytes per LDS row of A
+  constexpr int NPA = ARB / 16;
+  constexpr int AB = BM * ARB, WB = BN * 2 * KC;
+  constexpr int NT = 64 * NW;                   // threads of a k group
+  constexpr int WM = BM / 2, WN = BN / (NW / 2);  // a wave's tile
+  constexpr int FM = WM / 16, FN = WN / 16;     // 16 x 16 blocks per wave
+  constexpr int WL = 2048 / NT;                 // 16-byte loads of W per thread and chunk
+  constexpr int AL = LND ? 1 : BM * KC / 8 / NT;  // 16-byte loads of bf16 A per thread and chunk
+  static_assert(LND || BM * KC % (8 * NT) == 0, "the bf16 chunk splits over the threads");
+  constexpr int GB = AB + WB;  // LDS bytes per k group
+  static_assert(LND == 0 || KG == 1, "the panel serves one k group");
+  static_assert(KG == 1 || FM * FN * 16 * NT <= GB, "a group's accumulators fit its chunk buffers");
+  __shared__ __attribute__((aligned(1024))) uint8_t lds_all[KG * GB];
+  const int tid = threadIdx.x % NT, lane = tid & 63;
+  const int kg = __builtin_amdgcn_readfirstlane(threadIdx.x / NT), w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  uint8_t* lds = lds_all + kg * GB;
+  uint8_t* wl = lds + AB;
+  // an XCD takes a contiguous range of items: whole column tiles, whose W rows
+  // all their row tiles then find in one L2
+  const int n_items = p.mt * p.nt;
+  if ((int)blockIdx.x >= 8 * p.per_xcd) {
+    static_assert(GB >= kFoldLds, "the fold's rows and partial sums fit");
+    if (threadIdx.x >= 256) return;
+    if (p.fold.d == 512) psm_fold<512>(p.fold, blockIdx.x - 8 * p.per_xcd, reinterpret_cast<float*>(lds));
+    else psm_fold<256>(p.fold, blockIdx.x - 8 * p.per_xcd, reinterpret_cast<float*>(lds));
+    return;
+  }
+  const int item = (blockIdx.x & 7) * p.per_xcd + (blockIdx.x >> 3);
+  if (p.cu && blockIdx.x == 0)
+    for (int t = tid; t <= p.B; t += NT) p.cu[t] = t * p.T;
+  if (item >= n_items) return;
+  const int m0 = (item % p.mt) * BM, n0 = (item / p.mt) * BN;
+  const int K = p.K, nch = (K + KC * KG - 1) / (KC * KG);  // chunks per k group: KG*c + kg
+  auto swz_w = [](int row) { return NPW >= 16 ? row & 15 : (row >> 1) & (NPW - 1); };
+  auto swz_a = [](int row) { return NPA >= 16 ? row & 15 : (row >> 1) & (NPA - 1); };
+
+  // ---- chunk loads into registers: W (fp32) and, without the panel, A (bf16)
+  float4 wr[2][WL];
+  psm_u32x4 ar[2][AL];
+  auto load_chunk = [&](int c, float4 (&wd)[WL], psm_u32x4 (&ad)[AL]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < WL; ++i) {
+      const int q = tid + NT * i, row = q / (KC / 4), col = (KG * c + kg) * KC + (q % (KC / 4)) * 4;
+      // columns past K (a last chunk cut short) are zero
+      wd[i] = col < K ? *reinterpret_cast<const float4*>(p.W + (size_t)(n0 + row) * K + col) : make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+    if constexpr (LND == 0) {
+#pragma unroll
+      for (int i = 0; i < AL; ++i) {
+        const int q = tid + NT * i, row = q / NPW, col = (KG * c + kg) * KC + (q % NPW) * 8;
+        ad[i] = col < K ? *reinterpret_cast<const psm_u32x4*>(p.x + (size_t)min(m0 + row, p.M - 1) * K + col) : psm_u32x4{0, 0, 0, 0};
+      }
     }
   };
-  f32x16 acc;
+  auto store_chunk = [&](const float4 (&wd)[WL], const psm_u32x4 (&ad)[AL]) __attribute__((always_inline)) {
+    if constexpr (LND == 0) {
 #pragma unroll
-  for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-  // chunks of CH k16 steps: the chunk's loads are issued before its MFMAs
-  constexpr int CH = 4;
-  int k = 0;
-  for (; k + 16 * CH <= kw; k += 16 * CH) {
-    bf16x8 av[CH];
-    float4 bv0[CH], bv1[CH];
-#pragma unroll
-    for (int c = 0; c < CH; ++c) {
-      av[c] = a_op(k + 16 * c);
-      bv0[c] = *reinterpret_cast<const float4*>(bp + k + 16 * c);
-      bv1[c] = *reinterpret_cast<const float4*>(bp + k + 16 * c + 4);
+      for (int i = 0; i < AL; ++i) {
+        const int q = tid + NT * i, row = q / NPW, pc = q % NPW;
+        *reinterpret_cast<psm_u32x4*>(lds + row * ARB + ((pc ^ swz_a(row)) * 16)) = ad[i];
+      }
     }
 #pragma unroll
-    for (int c = 0; c < CH; ++c) {
-      const float bv[8] = {bv0[c].x, bv0[c].y, bv0[c].z, bv0[c].w, bv1[c].x, bv1[c].y, bv1[c].z, bv1[c].w};
-      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[c], pack_bf16x8(bv), acc, 0, 0, 0);
+    for (int i = 0; i < WL; ++i) {
+      const int q = tid + NT * i, row = q / (KC / 4), c4 = q % (KC / 4);
+      const psm_u32x2 v = {psm_pk(wd[i].x, wd[i].y), psm_pk(wd[i].z, wd[i].w)};
+      *reinterpret_cast<psm_u32x2*>(wl + row * (2 * KC) + (((c4 >> 1) ^ swz_w(row)) * 16) + (c4 & 1) * 8) = v;
     }
-  }
-  for (; k < kw; k += 16) {
-    const bf16x8 a = a_op(k);
-    const float4 b0 = *reinterpret_cast<const float4*>(bp + k);
-    const float4 b1 = *reinterpret_cast<const float4*>(bp + k + 4);
-    const float bv[8] = {b0.x, b0.y, b0.z, b0.w, b1.x, b1.y, b1.z, b1.w};
-    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, pack_bf16x8(bv), acc, 0, 0, 0);
-  }
+  };
+
+  if constexpr (LND != 0) {
+    // ---- the normalised rows: row 4*NW*it + 4*w + lane/16, lane li of its 16
+    // holding columns 4*(li + 16*j) .. +3
+    constexpr int J = LND / 64, IT = BM / (4 * NW);
+    const int li = lane & 15, r4 = 4 * w + (lane >> 4);
+    auto load_row = [&](int it, float4 (&x)[J]) __attribute__((always_inline)) {
+      const float4* xr = reinterpret_cast<const float4*>(p.src + (size_t)min(m0 + 4 * NW * it + r4, p.M - 1) * LND) + li;
 #pragma unroll
-  for (int r = 0; r < 16; ++r) red[w][r][lane] = acc[r];
-  __syncthreads();
-  // wave w finishes accumulator registers 4w .. 4w+3 of the block
-  const int col = n0 + l32;
-  const float bc = bias[col];
+      for (int j = 0; j < J; ++j) x[j] = xr[16 * j];
+    };
+    constexpr int XD = IT < 4 * 256 / LND ? IT : 4 * 256 / LND;  // rows in flight per lane
+    float4 x[XD][J], gg[J], bb[J];
 #pragma unroll
-  for (int rr = 0; rr < 4; ++rr) {
-    const int r = 4 * w + rr;
-    const int row = m0 + psm_acc_row(r, hl);
-    const float val = (((red[0][r][lane] + red[1][r][lane]) + red[2][r][lane]) + red[3][r][lane]) + bc;
-    if (row >= M) continue;
+    for (int it = 0; it < XD; ++it) load_row(it, x[it]);
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+      gg[j] = reinterpret_cast<const float4*>(p.g)[li + 16 * j];
+      bb[j] = reinterpret_cast<const float4*>(p.bt)[li + 16 * j];
+    }
+    load_chunk(0, wr[0], ar[0]);
+    auto norm_row = [&](int it, const float4 (&x)[J]) __attribute__((always_inline)) {
+      float s = 0.f;
+#pragma unroll
+      for (int j = 0; j < J; ++j) s += (x[j].x + x[j].y) + (x[j].z + x[j].w);
+      const float mu = row16_sum(s) * (1.f / LND);
+      float v = 0.f;
+#pragma unroll
+      for (int j = 0; j < J; ++j) {
+        const float a = x[j].x - mu, b = x[j].y - mu, c = x[j].z - mu, e = x[j].w - mu;
+        v = fmaf(a, a, fmaf(b, b, fmaf(c, c, fmaf(e, e, v))));
+      }
+      const float rstd = 1.f / sqrtf(row16_sum(v) * (1.f / LND) + 1e-5f);
+      const int row = 4 * NW * it + r4;
+#pragma unroll
+      for (int j = 0; j < J; ++j) {
+        const int c4 = li + 16 * j;
+        const psm_u32x2 y = {psm_pk(fmaf((x[j].x - mu) * rstd, gg[j].x, bb[j].x), fmaf((x[j].y - mu) * rstd, gg[j].y, bb[j].y)),
+                             psm_pk(fmaf((x[j].z - mu) * rstd, gg[j].z, bb[j].z), fmaf((x[j].w - mu) * rstd, gg[j].w, bb[j].w))};
+        *reinterpret_cast<psm_u32x2*>(lds + row * ARB + (((c4 >> 1) ^ swz_a(row)) * 16) + (c4 & 1) * 8) = y;
+      }
+    };
+#pragma unroll
+    for (int it = 0; it < IT; ++it) {
+      norm_row(it, x[it % XD]);
+      if (it + XD < IT) load_row(it + XD, x[it % XD]);
+    }
+  } else {
+    load_chunk(0, wr[0], ar[0]);
+  }
+  if (nch > 1) load_chunk(1, wr[1], ar[1]);
+
+  const int wm = w & 1, wn = w >> 1;  // the wave's tile
+  const int l16 = lane & 15, kq = lane >> 4;
+  f32x4 acc[FM][FN];
+#pragma unroll
+  for (int i = 0; i < FM; ++i)
+#pragma unroll
+    for (int j = 0; j < FN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  auto chunk = [&](int c, float4 (&wd)[WL], psm_u32x4 (&ad)[AL]) __attribute__((always_inline)) {
+    store_chunk(wd, ad);
+    __syncthreads();
+    if (c + 2 < nch) load_chunk(c + 2, wd, ad);
+#pragma unroll
+    for (int ks = 0; ks < KC / 32; ++ks) {
+      const int pw = 4 * ks + kq, pa = (LND ? c * (KC / 8) : 0) + pw;
+      if (LND == 0 || c * KC + 32 * ks < LND) {
+        bf16x8 a[FM], b[FN];
+#pragma unroll
+        for (int i = 0; i < FM; ++i) {
+          const int row = wm * WM + 16 * i + l16;
+          a[i] = *reinterpret_cast<const bf16x8*>(lds + row * ARB + ((pa ^ swz_a(row)) * 16));
+        }
+#pragma unroll
+        for (int j = 0; j < FN; ++j) {
+          const int row = wn * WN + 16 * j + l16;
+          b[j] = *reinterpret_cast<const bf16x8*>(wl + row * (2 * KC) + ((pw ^ swz_w(row)) * 16));
+        }
+#pragma unroll
+        for (int i = 0; i < FM; ++i)
+#pragma unroll
+          for (int j = 0; j < FN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[j], a[i], acc[i][j], 0, 0, 0);
+      }
+    }
+    __syncthreads();
+  };
+  // what the epilogue reads is asked for now, with the first chunks
+  float4 bc[FN], rs[MODE == kOutResid ? FM : 1][FN];
+#pragma unroll
+  for (int j = 0; j < FN; ++j) {
+    const int n = n0 + wn * WN + 16 * j + 4 * kq;
+    bc[j] = *reinterpret_cast<const float4*>(p.bias + n);
     if constexpr (MODE == kOutResid) {
-      const size_t i = (size_t)row * N + col;
-      h[i] = (rsrc ? rsrc[i] : h[i]) + val;
-    } else if constexpr (MODE == kOutGelu) {
-      out0[(size_t)row * N + col] = f32_to_bf16_bits(gelu_erf(val));
-    } else {
-      const int wsplit = N / nsplit, j = col / wsplit;
-      uint16_t* o = j == 0 ? out0 : (j == 1 ? out1 : out2);
-      o[(size_t)row * wsplit + (col - j * wsplit)] = f32_to_bf16_bits(val);
+#pragma unroll
+      for (int i = 0; i < FM; ++i)
+        rs[i][j] = *reinterpret_cast<const float4*>(
+            p.rsrc + (size_t)min(m0 + wm * WM + 16 * i + l16, p.M - 1) * p.N + n);
+    }
+  }
+  for (int c = 0; c < nch; c += 2) {
+    chunk(c, wr[0], ar[0]);
+    if (c + 1 < nch) chunk(c + 1, wr[1], ar[1]);
+  }
+
+  if constexpr (KG > 1) {
+    // the k groups' sums, added in group order (the last chunk's reads are done)
+    if (kg > 0) {
+#pragma unroll
+      for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j) *reinterpret_cast<f32x4*>(lds + ((i * FN + j) * NT + tid) * 16) = acc[i][j];
+    }
+    __syncthreads();
+    if (kg > 0) return;
+#pragma unroll
+    for (int x = 1; x < KG; ++x)
+#pragma unroll
+      for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j)
+          acc[i][j] += *reinterpret_cast<const f32x4*>(lds_all + x * GB + ((i * FN + j) * NT + tid) * 16);
+  }
+
+  // ---- lane: row l16 of block i, columns 4*kq .. +3 of block j
+#pragma unroll
+  for (int j = 0; j < FN; ++j) {
+    const int n = n0 + wn * WN + 16 * j + 4 * kq;
+#pragma unroll
+    for (int i = 0; i < FM; ++i) {
+      const int row = m0 + wm * WM + 16 * i + l16;
+      if (row >= p.M) continue;
+      float v[4] = {acc[i][j][0] + bc[j].x, acc[i][j][1] + bc[j].y, acc[i][j][2] + bc[j].z, acc[i][j][3] + bc[j].w};
+      if constexpr (MODE == kOutResid) {
+        const float4 r = rs[i][j];
+        *reinterpret_cast<float4*>(p.h + (size_t)row * p.N + n) = make_float4(r.x + v[0], r.y + v[1], r.z + v[2], r.w + v[3]);
+      } else {
+        int ld = p.N, col = n;
+        uint16_t* o = p.o0;
+        if constexpr (MODE == kOutBf16) {
+          ld = p.N / 3;
+          const int sp = n / ld;
+          col = n - sp * ld;
+          o = sp == 0 ? p.o0 : (sp == 1 ? p.o1 : p.o2);
+        } else {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) v[e] = gelu_erf(v[e]);
+        }
+        *reinterpret_cast<psm_u32x2*>(o + (size_t)row * ld + col) = psm_u32x2{psm_pk(v[0], v[1]), psm_pk(v[2], v[3])};
+      }
     }
   }
 }
 
-// View logit of (view blockIdx.x, sample blockIdx.y): q = latent W_cq^T + b_cq,
-// p = softmax_t(q . k_t / sqrt(d)), z = sum_t p_t v_t, logit = w_head . z + b_head.
-template <int EPT>
-__global__ __launch_bounds__(256) void psm_cross_kernel(const uint16_t* __restrict__ kc,
-                                                        const uint16_t* __restrict__ vc,
-                                                        const float* __restrict__ latents,
-                                                        const float* __restrict__ w_cq, const float* __restrict__ b_cq,
-                                                        const float* __restrict__ w_head,
-                                                        const float* __restrict__ b_head, float* __restrict__ logit,
-                                                        int T, int n_views) {
-  constexpr int d = EPT * 256;
-  const int v = blockIdx.x, b = blockIdx.y, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  __shared__ float q[d];
-  __shared__ float red[8];
-  extern __shared__ float p[];  // [T]
-  // query of the latent: thread j computes elements j, j + 256, ...
+// View logits of views VPW*blockIdx.x .. and sample blockIdx.y from the folded
+// latents: with x_t the final LayerNorm of token t, logit_v = sum_t
+// softmax_t(x_t . u_v / sqrt(d)) (x_t . g_v) + cst_v (a constant in the softmax
+// argument cancels). 16 lanes take a token row (NG rows at a time), hold it in
+// registers and keep a running softmax of their rows; the gain and bias of the
+// norm are folded into the lane's share of u and g first. fp32 throughout.
+constexpr int psm_head_threads(int D) { return D == 512 ? 512 : 1024; }  // what the registers allow
+template <int D>
+__global__ __launch_bounds__(psm_head_threads(D)) void psm_head_kernel(const float* __restrict__ h, const float* __restrict__ gf,
+                                                        const float* __restrict__ bf, const float* __restrict__ u,
+                                                        const float* __restrict__ g, const float* __restrict__ cst,
+                                                        float* __restrict__ logit, int T, int n_views) {
+  constexpr int J = D / 64, VPW = 512 / D;  // float4 pieces per lane; views per workgroup
+  constexpr int NG = psm_head_threads(D) / 16;
+  __shared__ float part[3][VPW][NG];
+  const int tid = threadIdx.x, li = tid & 15, grp = tid >> 4, b = blockIdx.y, v0 = blockIdx.x * VPW;
+  const float4* hb = reinterpret_cast<const float4*>(h + (size_t)b * T * D) + li;
+  auto load_row = [&](int t, float4 (&x)[J]) __attribute__((always_inline)) {
 #pragma unroll
-  for (int e = 0; e < EPT; ++e) {
-    const int j = tid + 256 * e;
-    float s = b_cq[j];
-    const float* wr = w_cq + (size_t)j * d;
-    const float* lr = latents + (size_t)v * d;
-#pragma unroll 16
-    for (int i = 0; i < d; ++i) s = fmaf(lr[i], wr[i], s);
-    q[j] = s;
+    for (int j = 0; j < J; ++j) x[j] = hb[(size_t)min(t, T - 1) * (D / 4) + 16 * j];
+  };
+  float4 x[J], nx[J], uu[VPW][J], gg[VPW][J];
+  load_row(grp, x);
+  float cg[VPW];
+#pragma unroll
+  for (int v = 0; v < VPW; ++v) {
+    const int vv = min(v0 + v, n_views - 1);
+    cg[v] = 0.f;
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+      const float4 w = reinterpret_cast<const float4*>(gf)[li + 16 * j], o = reinterpret_cast<const float4*>(bf)[li + 16 * j];
+      const float4 a = reinterpret_cast<const float4*>(u + (size_t)vv * D)[li + 16 * j];
+      const float4 c = reinterpret_cast<const float4*>(g + (size_t)vv * D)[li + 16 * j];
+      uu[v][j] = make_float4(a.x * w.x, a.y * w.y, a.z * w.z, a.w * w.w);
+      gg[v][j] = make_float4(c.x * w.x, c.y * w.y, c.z * w.z, c.w * w.w);
+      cg[v] = fmaf(c.x, o.x, fmaf(c.y, o.y, fmaf(c.z, o.z, fmaf(c.w, o.w, cg[v]))));
+    }
+    cg[v] = row16_sum(cg[v]);
   }
-  __syncthreads();
-  const float scale = 1.f / sqrtf((float)d);
-  float mx = -INFINITY;
-  for (int t = tid; t < T; t += 256) {
-    const uint16_t* kr = kc + ((size_t)b * T + t) * d;
+  const float scale = kLog2e / sqrtf((float)D);
+  float m[VPW], l[VPW], z[VPW];
+#pragma unroll
+  for (int v = 0; v < VPW; ++v) {
+    m[v] = -INFINITY;
+    l[v] = 0.f;
+    z[v] = 0.f;
+  }
+  for (int t = grp; t < T; t += NG) {
+    if (t + NG < T) load_row(t + NG, nx);
     float s = 0.f;
-#pragma unroll 16
-    for (int i = 0; i < d; ++i) s = fmaf(q[i], bf16_bits_to_f32(kr[i]), s);
-    s *= scale;
-    p[t] = s;
-    mx = fmaxf(mx, s);
+#pragma unroll
+    for (int j = 0; j < J; ++j) s += (x[j].x + x[j].y) + (x[j].z + x[j].w);
+    const float mu = row16_sum(s) * (1.f / D);
+    float q = 0.f;
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+      x[j] = make_float4(x[j].x - mu, x[j].y - mu, x[j].z - mu, x[j].w - mu);
+      q = fmaf(x[j].x, x[j].x, fmaf(x[j].y, x[j].y, fmaf(x[j].z, x[j].z, fmaf(x[j].w, x[j].w, q))));
+    }
+    const float rstd = 1.f / sqrtf(row16_sum(q) * (1.f / D) + 1e-5f);
+#pragma unroll
+    for (int v = 0; v < VPW; ++v) {
+      float a = 0.f, c = 0.f;
+#pragma unroll
+      for (int j = 0; j < J; ++j) {
+        a = fmaf(x[j].x, uu[v][j].x, fmaf(x[j].y, uu[v][j].y, fmaf(x[j].z, uu[v][j].z, fmaf(x[j].w, uu[v][j].w, a))));
+        c = fmaf(x[j].x, gg[v][j].x, fmaf(x[j].y, gg[v][j].y, fmaf(x[j].z, gg[v][j].z, fmaf(x[j].w, gg[v][j].w, c))));
+      }
+      a = row16_sum(a) * rstd * scale;
+      c = row16_sum(c) * rstd;
+      const float mn = fmaxf(m[v], a);
+      const float al = __builtin_amdgcn_exp2f(m[v] - mn), e = __builtin_amdgcn_exp2f(a - mn);  // first row: al = exp2(-inf) = 0
+      l[v] = fmaf(l[v], al, e);
+      z[v] = fmaf(z[v], al, e * c);
+      m[v] = mn;
+    }
+#pragma unroll
+    for (int j = 0; j < J; ++j) x[j] = nx[j];
   }
 #pragma unroll
-  for (int m = 1; m < kWave; m <<= 1) mx = fmaxf(mx, __shfl_xor(mx, m, kWave));
-  if (lane == 0) red[w] = mx;
+  for (int v = 0; v < VPW; ++v)
+    if (li == 0) {
+      part[0][v][grp] = m[v];
+      part[1][v][grp] = l[v];
+      part[2][v][grp] = z[v];
+    }
   __syncthreads();
-  mx = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
-  float sum = 0.f;
-  for (int t = tid; t < T; t += 256) {
-    const float e = __expf(p[t] - mx);
-    p[t] = e;
-    sum += e;
-  }
+  // wave v merges the groups of view v (a group without a row: max -inf, sums 0)
+  const int v = tid >> 6, lane = tid & 63, gl = min(lane, NG - 1);
+  if (v >= VPW || v0 + v >= n_views) return;
+  const float mm = lane < NG ? part[0][v][gl] : -INFINITY;
+  float mx = mm;
 #pragma unroll
-  for (int m = 1; m < kWave; m <<= 1) sum += __shfl_xor(sum, m, kWave);
-  __syncthreads();
-  if (lane == 0) red[4 + w] = sum;
-  __syncthreads();
-  const float inv = 1.f / (((red[4] + red[5]) + red[6]) + red[7]);
-  // z and its dot with the head weights
-  float dotp = 0.f;
+  for (int i = 1; i < kWave; i <<= 1) mx = wave_max_xor(mx, i);
+  const float wgt = __builtin_amdgcn_exp2f(mm - mx);
+  const float ls = psm_wave_sum(part[1][v][gl] * wgt), zs = psm_wave_sum(part[2][v][gl] * wgt);
+  float cgv = cg[0];
 #pragma unroll
-  for (int e = 0; e < EPT; ++e) {
-    const int j = tid + 256 * e;
-    float z = 0.f;
-    for (int t = 0; t < T; ++t) z = fmaf(p[t], bf16_bits_to_f32(vc[((size_t)b * T + t) * d + j]), z);
-    dotp = fmaf(z * inv, w_head[(size_t)v * d + j], dotp);
-  }
-#pragma unroll
-  for (int m = 1; m < kWave; m <<= 1) dotp += __shfl_xor(dotp, m, kWave);
-  __syncthreads();
-  if (lane == 0) red[w] = dotp;
-  __syncthreads();
-  if (tid == 0) logit[(size_t)b * n_views + v] = ((red[0] + red[1]) + red[2]) + red[3] + b_head[v];
+  for (int i = 1; i < VPW; ++i) cgv = v == i ? cg[i] : cgv;
+  if (lane == 0) logit[(size_t)b * n_views + v0 + v] = zs / ls + (cgv + cst[v0 + v]);
 }
 
-template <int MODE, bool LNIN>
-void gemm(const uint16_t* x, const float* src, const float* g, const float* bt, const float* W, const float* bias,
-          int M, int N, int K, uint16_t* o0, uint16_t* o1, uint16_t* o2, int nsplit, float* h, const float* rsrc,
-          int32_t* cu, int B, int T, hipStream_t s) {
-  hipLaunchKernelGGL((psm_gemm_kernel<MODE, LNIN>), dim3((M + 31) / 32, N / 32), dim3(256), 0, s, x, src, g, bt, W,
-                     bias, M, N, K, o0, o1, o2, nsplit, h, rsrc, cu, B, T);
+template <int MODE, int LND, int BM, int BN, int NW, int KG>
+void gemm_launch(PsmGemm& p, hipStream_t s) {
+  p.mt = (p.M + BM - 1) / BM;
+  p.nt = p.N / BN;
+  p.per_xcd = (p.mt * p.nt + 7) / 8;
+  const int grid = 8 * p.per_xcd + psm_fold_blocks(p.fold.stage, p.fold.d);
+  hipLaunchKernelGGL((psm_gemm_kernel<MODE, LND, BM, BN, NW, KG>), dim3(grid), dim3(64 * NW * KG), 0, s, p);
 }
 
+// Tile by the number of workgroups it gives (256 CUs). A 32 x 32 tile is one
+// round trip of loads per workgroup, the shortest launch while the grid is
+// small; past 192 tiles of 64 x 64 their halved cache traffic wins (batch 8 of
+// 128 tokens, d 256: QKV 6.4 against 8.0 us, up 7.9 against 11.0 us), with eight
+// waves to share a tile's loads and norm (four: 7.1 and 8.8 us). From 512 tiles
+// of 64 x 128 on, bandwidth counts and four waves of 32 x 64 read LDS least
+// (3200 x 2048 x 512: 36 us, 64 x 64 tiles 49 us, eight waves 51 us); without
+// the norm four waves serve 64 x 64 too (3200 x 512 x 2048: 18.4 against 23.4).
+// A long k range on few 32 x 32 tiles is shared by two wave groups, so that
+// all of it is in flight at once (128 x 256 x 1024: 6.3 against 7.0 us).
+template <int MODE, int LND>
+void gemm(PsmGemm& p, hipStream_t s) {
+  auto tiles = [&](int bm, int bn) { return (long long)((p.M + bm - 1) / bm) * (p.N / bn); };
+  if (p.N % 128 == 0 && tiles(64, 128) >= 512) gemm_launch<MODE, LND, 64, 128, 4, 1>(p, s);
+  else if (tiles(64, 64) >= 192) gemm_launch<MODE, LND, 64, 64, LND ? 8 : 4, 1>(p, s);
+  else if (LND == 0 && p.K >= 512 && tiles(32, 32) < 256) gemm_launch<MODE, LND, 32, 32, 4, LND ? 1 : 2>(p, s);
+  else gemm_launch<MODE, LND, 32, 32, 4, 1>(p, s);
+}
+
+template <int D>
 hipError_t run(const PsmArgs& a, hipStream_t s) {
   const PsmLayout L = psm_layout(a.B, a.T, a.d, a.d_ff, a.n_views, a.n_layers);
   const int M = a.B * a.T, d = a.d, dff = a.d_ff, B = a.B, T = a.T;
@@ -233,6 +569,24 @@ hipError_t run(const PsmArgs& a, hipStream_t s) {
   uint16_t* ff = reinterpret_cast<uint16_t*>(ws + L.ff_off);
   int32_t* cu = reinterpret_cast<int32_t*>(ws + L.cu_off);
   const float* P = a.params;
+  const float* fp = P + (size_t)a.n_layers * L.layer_params;
+  const float* lnf_g = fp;
+  const float* lnf_b = lnf_g + d;
+  PsmFold fold;
+  fold.d = d;
+  fold.n_views = a.n_views;
+  fold.lat = lnf_b + d;
+  fold.w_cq = fold.lat + (size_t)a.n_views * d;
+  fold.b_cq = fold.w_cq + (size_t)d * d;
+  fold.w_ck = fold.b_cq + d;
+  fold.w_cv = fold.w_ck + (size_t)d * d + d;  // b_ck adds a constant to every token's logit: no effect
+  fold.b_cv = fold.w_cv + (size_t)d * d;
+  fold.w_hd = fold.b_cv + d;
+  fold.b_hd = fold.w_hd + (size_t)a.n_views * d;
+  fold.qv = reinterpret_cast<float*>(ws + L.fold_off);
+  fold.u = fold.qv + (size_t)a.n_views * d;
+  fold.g = fold.u + (size_t)a.n_views * d;
+  fold.cst = fold.g + (size_t)a.n_views * d;
   for (int i = 0; i < a.n_layers; ++i) {
     const float* lp = P + (size_t)i * L.layer_params;
     const float* ln1_g = lp;
@@ -247,10 +601,29 @@ hipError_t run(const PsmArgs& a, hipStream_t s) {
     const float* b_up = w_up + (size_t)dff * d;
     const float* w_dn = b_up + dff;
     const float* b_dn = w_dn + (size_t)d * dff;
+    auto args = [&](const float* W, const float* bias, int N, int K, int stage) {
+      PsmGemm p{};
+      p.W = W;
+      p.bias = bias;
+      p.M = M;
+      p.N = N;
+      p.K = K;
+      p.fold = fold;
+      p.fold.stage = stage;
+      return p;
+    };
     // the first layer reads the embeddings; its first residual add seeds h
-    const float* hin = i == 0 ? a.emb : h;
-    gemm<kOutBf16, true>(nullptr, hin, ln1_g, ln1_b, w_qkv, b_qkv, M, 3 * d, d, q, k, v, 3, nullptr, nullptr,
-                         i == 0 ? cu : nullptr, B, T, s);
+    PsmGemm p1 = args(w_qkv, b_qkv, 3 * d, d, i == 0 ? 1 : 0);
+    p1.src = i == 0 ? a.emb : h;
+    p1.g = ln1_g;
+    p1.bt = ln1_b;
+    p1.o0 = q;
+    p1.o1 = k;
+    p1.o2 = v;
+    p1.cu = i == 0 ? cu : nullptr;
+    p1.B = B;
+    p1.T = T;
+    gemm<kOutBf16, D>(p1, s);
     AttnArgs at;
     at.in_dtype = LITEVLM_BF16;
     at.out_dtype = LITEVLM_BF16;
@@ -269,36 +642,27 @@ hipError_t run(const PsmArgs& a, hipStream_t s) {
     at.o = att;
     const hipError_t e = launch_prefill_attn(at, s);
     if (e != hipSuccess) return e;
-    gemm<kOutResid, false>(att, nullptr, nullptr, nullptr, w_o, b_o, M, d, d, nullptr, nullptr, nullptr, 1, h,
-                           i == 0 ? a.emb : nullptr, nullptr, B, T, s);
-    gemm<kOutGelu, true>(nullptr, h, ln2_g, ln2_b, w_up, b_up, M, dff, d, ff, nullptr, nullptr, 1, nullptr, nullptr,
-                         nullptr, B, T, s);
-    gemm<kOutResid, false>(ff, nullptr, nullptr, nullptr, w_dn, b_dn, M, d, dff, nullptr, nullptr, nullptr, 1, h,
-                           nullptr, nullptr, B, T, s);
+    PsmGemm p2 = args(w_o, b_o, d, d, i == 0 ? 2 : 0);
+    p2.x = att;
+    p2.h = h;
+    p2.rsrc = i == 0 ? a.emb : h;
+    gemm<kOutResid, 0>(p2, s);
+    PsmGemm p3 = args(w_up, b_up, dff, d, 0);
+    p3.src = h;
+    p3.g = ln2_g;
+    p3.bt = ln2_b;
+    p3.o0 = ff;
+    gemm<kOutGelu, D>(p3, s);
+    PsmGemm p4 = args(w_dn, b_dn, d, dff, 0);
+    p4.x = ff;
+    p4.h = h;
+    p4.rsrc = h;
+    gemm<kOutResid, 0>(p4, s);
   }
-  const float* fp = P + (size_t)a.n_layers * L.layer_params;
-  const float* lnf_g = fp;
-  const float* lnf_b = lnf_g + d;
-  const float* lat = lnf_b + d;
-  const float* w_cq = lat + (size_t)a.n_views * d;
-  const float* b_cq = w_cq + (size_t)d * d;
-  const float* w_ck = b_cq + d;
-  const float* b_ck = w_ck + (size_t)d * d;
-  const float* w_cv = b_ck + d;
-  const float* b_cv = w_cv + (size_t)d * d;
-  const float* w_hd = b_cv + d;
-  const float* b_hd = w_hd + (size_t)a.n_views * d;
-  gemm<kOutBf16, true>(nullptr, h, lnf_g, lnf_b, w_ck, b_ck, M, d, d, q, nullptr, nullptr, 1, nullptr, nullptr,
-                       nullptr, B, T, s);
-  gemm<kOutBf16, true>(nullptr, h, lnf_g, lnf_b, w_cv, b_cv, M, d, d, k, nullptr, nullptr, 1, nullptr, nullptr,
-                       nullptr, B, T, s);
-  const size_t pbytes = (size_t)T * sizeof(float);
-  if (d == 512)
-    hipLaunchKernelGGL((psm_cross_kernel<2>), dim3(a.n_views, B), dim3(256), pbytes, s, q, k, lat, w_cq, b_cq, w_hd,
-                       b_hd, a.view_logit, T, a.n_views);
-  else
-    hipLaunchKernelGGL((psm_cross_kernel<1>), dim3(a.n_views, B), dim3(256), pbytes, s, q, k, lat, w_cq, b_cq, w_hd,
-                       b_hd, a.view_logit, T, a.n_views);
+  constexpr int VPW = 512 / D;
+  hipLaunchKernelGGL((psm_head_kernel<D>), dim3((a.n_views + VPW - 1) / VPW, B),
+                     dim3(psm_head_threads(D)), 0, s, h, lnf_g, lnf_b,
+                     fold.u, fold.g, fold.cst, a.view_logit, T, a.n_views);
   return hipGetLastError();
 }
 
@@ -327,10 +691,16 @@ PsmLayout psm_layout(int B, int T, int d, int d_ff, int n_views, int n_layers) {
   off = a256(off + M * d_ff * 2);
   L.cu_off = off;
   off = a256(off + (size_t)(B + 1) * 4);
+  // the folded latents of up to LITEVLM_MAX_VIEWS views (the size is asked for
+  // without their number): q_v, u_v, g_v [d] and one constant each
+  L.fold_off = off;
+  off = a256(off + (size_t)LITEVLM_MAX_VIEWS * (3 * (size_t)d + 1) * 4);
   L.total = off;
   return L;
 }
 
-hipError_t launch_psm_forward(const PsmArgs& a, hipStream_t stream) { return run(a, stream); }
+hipError_t launch_psm_forward(const PsmArgs& a, hipStream_t stream) {
+  return a.d == 512 ? run<512>(a, stream) : run<256>(a, stream);
+}
 
 }  // namespace litevlm

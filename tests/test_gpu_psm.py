@@ -55,3 +55,27 @@ def test_psm_is_deterministic():
     a, _ = run(c, seed=5200)
     b, _ = run(c, seed=5200)
     assert torch.equal(a, b)
+
+
+# Where the tiles, chunks and folds end: one token; rows past a 32-row tile; k
+# ranges shorter than a chunk and cut short in the last one; more views than a
+# pass of the fold takes, an odd number of them; each tile size of the GEMMs (64
+# x 64 from 192 tiles on, 64 x 128 from 512) with a last row tile cut short.
+EDGES = [
+    ("one token, one view", dict(B=1, T=1, d=256, H=4, dff=64, N=1, L=1)),
+    ("65 rows, d_ff 320", dict(B=1, T=65, d=256, H=2, dff=320, N=9, L=2)),
+    ("64 views, d 512, d_ff 576", dict(B=3, T=33, d=512, H=8, dff=576, N=64, L=1)),
+    ("64 x 64 tiles, 1010 rows", dict(B=5, T=202, d=256, H=4, dff=1024, N=5, L=2)),
+    ("64 x 64 tiles, d 512, 1450 rows", dict(B=2, T=725, d=512, H=4, dff=1088, N=3, L=1)),
+    ("64 x 128 tiles, d 512, 2060 rows", dict(B=4, T=515, d=512, H=8, dff=2048, N=6, L=1)),
+    ("64 x 128 tiles, d 256, 5500 rows", dict(B=20, T=275, d=256, H=4, dff=1024, N=6, L=1)),
+]
+
+
+@pytest.mark.parametrize("name,c", EDGES)
+def test_psm_edges(name, c):
+    out, ref = run(c, seed=5300 + c["T"])
+    err = np.abs(out.cpu().numpy().astype(np.float64) - ref)
+    # the bound of the shapes above: bf16 GEMM inputs over at most two layers
+    assert np.all(err <= PSM_ATOL + PSM_RTOL * np.abs(ref)), f"{name}: max err {err.max():.3g}"
+    log(f"{name}: logits max abs err {err.max():.2e} (|ref| max {np.abs(ref).max():.2f})")
