@@ -15,6 +15,7 @@
 // A operand in a permuted order chosen so that the exponentiated accumulator
 // of S^T is already the B operand of the P.V product; V stays row-major in LDS
 // and the LDS transpose reads (ds_read_b64_tr_b16 / _b8) build its A operand.
+#include <algorithm>
 #include <type_traits>
 
 #include "common.hpp"
@@ -80,8 +81,7 @@ __device__ __forceinline__ int tile_key(int nb, int rho) {
 // an XCD owns whole KV heads across the batch, so workgroups sharing K/V sit
 // behind the same L2 while ragged samples spread evenly over the XCDs, and
 // within an XCD the longest causal tiles start first.
-__device__ __forceinline__ bool decode_work(const AttnParams& p, int& b, int& h, int& mt) {
-  const int L = blockIdx.x;
+__device__ __forceinline__ bool decode_work(const AttnParams& p, int L, int& b, int& h, int& mt) {
   const int w = (L & 7) * p.per_xcd + (L >> 3);
   if (w >= p.n_work) return false;
   const int hh = w % p.G;
@@ -179,7 +179,7 @@ attn_bf16_kernel(AttnParams p) {
   __shared__ __attribute__((aligned(1024))) uint8_t kvl[4 * TB];
 
   int b, h, mt;
-  if (!decode_work(p, b, h, mt)) return;
+  if (!decode_work(p, (int)blockIdx.x, b, h, mt)) return;
   const int seq0 = p.cu[b];
   const int len = p.cu[b + 1] - seq0;
   const int m0 = mt * BM;
@@ -818,7 +818,7 @@ attn_fp8_kernel(AttnParams p) {
   __shared__ __attribute__((aligned(1024))) uint8_t kvl[4 * TB];
 
   int b, h, mt;
-  if (!decode_work(p, b, h, mt)) return;
+  if (!decode_work(p, (int)blockIdx.x, b, h, mt)) return;
   const int seq0 = p.cu[b];
   const int len = p.cu[b + 1] - seq0;
   const int m0 = mt * BM;
@@ -1032,68 +1032,209 @@ attn_fp8_kernel(AttnParams p) {
   }
 }
 
-// fp32 path: one lane per query row, K/V tiles of 64 keys staged in LDS,
-// plain FMAs. Meant for small fp32 problems.
-template <int D, bool CAUSAL, int OUT>
-__global__ void __launch_bounds__(64)
+// fp32 path on v_mfma_f32_16x16x4_f32. A workgroup owns QB blocks of 16 query
+// rows of one head; its NW waves take the 16-key tiles in turn (wave w tiles w,
+// w + NW, ...), each with a running (max, sum) and output of its own, and the
+// waves are merged through LDS in wave order. Operands come straight from global
+// memory: nothing is shared between the waves of a workgroup.
+//
+// Bound: the smallest calls (80 tokens, 4 heads: 12 workgroups of 8 waves) are
+// one chain of latencies, so the keys of a row are split over the waves; large
+// ones are bound by the fp32 matrix rate (twice the vector rate). Per call, against
+// one lane per query row with FMAs over 64-key LDS tiles: 64 tokens, 8/4 heads of
+// 64 65.8 -> 8.2 us; 200 tokens, 16/2 heads of 128 531 -> 10.4 us; 2 x 768
+// tokens, 32/8 heads of 128 2180 -> 170 us.
+//
+// S^T = K Q^T: lane l holds key (resp. query) l % 16 and, of the j-th 16 head
+// dims, the 4 at 4*(l / 16); MFMA (j, e) multiplies element e of these. Its
+// accumulator r of lane l is key 4*(l/16) + r of query l % 16, which is the B
+// operand of P.V step r as it stands. V enters that step as the A operand: lane
+// l holds dims 64*hd + 4*(l%16) + e of key 4*(l/16) + r, one 16-byte load for
+// the four blocks e, so o[hd][e][x] is dim 64*hd + 16*(l/16) + 4*x + e of query
+// l % 16.
+constexpr int kF32Waves = 8;
+
+template <int D, bool CAUSAL, int OUT, int QB>
+__global__ void __launch_bounds__(64 * kF32Waves)
 attn_fwd_f32_kernel(AttnParams p) {
-  constexpr int BN = 64;
-  __shared__ float Ksh[BN][D];
-  __shared__ float Vsh[BN][D];
+  constexpr int NW = kF32Waves, NJ = D / 16, HD = D / 64, RS = D + 4;  // RS: padded LDS row, against bank conflicts
+  __shared__ __attribute__((aligned(16))) float osh[NW][16][RS];
+  __shared__ float msh[NW][16], lsh[NW][16];
   const float* __restrict__ q = static_cast<const float*>(p.q);
   const float* __restrict__ k = static_cast<const float*>(p.k);
   const float* __restrict__ v = static_cast<const float*>(p.v);
-  int b, h, mt;
-  if (!decode_work(p, b, h, mt)) return;
-  const int seq0 = p.cu[b];
-  const int len = p.cu[b + 1] - seq0;
-  const int m0 = mt * 64;
-  if (m0 >= len) return;
-  const int g = h / p.G;
-  const int qi = m0 + threadIdx.x;
-  const bool q_ok = qi < len;
-  float qr[D], acc[D];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, l16 = lane & 15, lg = lane >> 4;
+  const size_t kvs = (size_t)p.Hkv * D;
+  for (int L = blockIdx.x; L < 8 * p.per_xcd; L += gridDim.x) {
+    int b, h, mt;
+    if (!decode_work(p, L, b, h, mt)) continue;
+    const int seq0 = p.cu[b];
+    const int len = p.cu[b + 1] - seq0;
+    const int m0 = mt * 16 * QB;
+    if (m0 >= len) continue;
+    const int g = h / p.G;
+    const float* kb = k + ((size_t)seq0 * p.Hkv + g) * D;
+    const float* vb = v + ((size_t)seq0 * p.Hkv + g) * D;
+    f32x4 qr[QB][NJ], o[QB][HD][4];
+    float m_run[QB], l_run[QB];
 #pragma unroll
-  for (int d = 0; d < D; ++d) {
-    qr[d] = q_ok ? q[((size_t)(seq0 + qi) * p.Hq + h) * D + d] : 0.f;
-    acc[d] = 0.f;
-  }
-  float m_run = -INFINITY, l_run = 0.f;
-  const int kend = CAUSAL ? min(len, m0 + 64) : len;
-  for (int k0 = 0; k0 < kend; k0 += BN) {
-    __syncthreads();
-    for (int c = threadIdx.x; c < BN * D; c += 64) {
-      const int key = c / D, d = c % D;
-      const bool ok = k0 + key < len;
-      const size_t idx = ((size_t)(seq0 + k0 + key) * p.Hkv + g) * D + d;
-      Ksh[key][d] = ok ? k[idx] : 0.f;
-      Vsh[key][d] = ok ? v[idx] : 0.f;
+    for (int qb = 0; qb < QB; ++qb) {
+      const int qi = min(m0 + 16 * qb + l16, len - 1);  // rows past the end repeat the last, and are not stored
+      const float* qp = q + ((size_t)(seq0 + qi) * p.Hq + h) * D + 4 * lg;
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) qr[qb][j] = *reinterpret_cast<const f32x4*>(qp + 16 * j);
+#pragma unroll
+      for (int hd = 0; hd < HD; ++hd)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[qb][hd][e] = f32x4{0.f, 0.f, 0.f, 0.f};
+      m_run[qb] = -INFINITY;
+      l_run[qb] = 0.f;
     }
-    __syncthreads();
-    const int nk = min(BN, kend - k0);
-    for (int j = 0; j < nk; ++j) {
-      const int key = k0 + j;
-      if (CAUSAL && key > qi) break;
-      float s = 0.f;
+    const int kend = CAUSAL ? min(len, m0 + 16 * QB) : len;
+    for (int k0 = 16 * w; k0 < kend; k0 += 16 * NW) {
+      f32x4 kr[NJ], vr[4][HD];
+      const float* kp = kb + (size_t)min(k0 + l16, len - 1) * kvs + 4 * lg;
 #pragma unroll
-      for (int d = 0; d < D; ++d) s = fmaf(qr[d], Ksh[j][d], s);
-      const float x = s * p.scale_log2;
-      const float m_new = fmaxf(m_run, x);
-      const float alpha = exp2f(m_run - m_new);
-      const float pj = exp2f(x - m_new);
-      l_run = l_run * alpha + pj;
+      for (int j = 0; j < NJ; ++j) kr[j] = *reinterpret_cast<const f32x4*>(kp + 16 * j);
+      f32x4 s[QB];
 #pragma unroll
-      for (int d = 0; d < D; ++d) acc[d] = fmaf(pj, Vsh[j][d], acc[d] * alpha);
-      m_run = m_new;
+      for (int qb = 0; qb < QB; ++qb) s[qb] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int j = 0; j < NJ; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int qb = 0; qb < QB; ++qb)
+            s[qb] = __builtin_amdgcn_mfma_f32_16x16x4f32(kr[j][e], qr[qb][j][e], s[qb], 0, 0, 0);
+      // with two row blocks the value operand takes the key operand's registers
+      if (QB > 1) __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const float* vp = vb + (size_t)min(k0 + 4 * lg + r, len - 1) * kvs + 4 * l16;
+#pragma unroll
+        for (int hd = 0; hd < HD; ++hd) vr[r][hd] = *reinterpret_cast<const f32x4*>(vp + 64 * hd);
+      }
+      // a tile that some row does not see whole
+      const bool edge = k0 + 16 > len || (CAUSAL && k0 + 15 > m0);
+      uint32_t vis[QB];
+#pragma unroll
+      for (int qb = 0; qb < QB; ++qb) {
+        vis[qb] = 15u;
+        if (edge) {
+          const int lim = min(len - 1, CAUSAL ? m0 + 16 * qb + l16 : len - 1);  // last visible key
+          const int n = min(max(lim - (k0 + 4 * lg) + 1, 0), 4);
+          vis[qb] = (1u << n) - 1u;
+        }
+        float x[4], mx = -INFINITY;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          x[r] = (vis[qb] >> r) & 1u ? s[qb][r] * p.scale_log2 : -INFINITY;
+          mx = fmaxf(mx, x[r]);
+        }
+        mx = max_xor32(max_xor16(mx));
+        const float m_new = fmaxf(m_run[qb], mx);
+        const bool none = m_new == -INFINITY;  // no visible key yet
+        const float alpha = none ? 1.f : __builtin_amdgcn_exp2f(m_run[qb] - m_new);
+        l_run[qb] *= alpha;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          s[qb][r] = none ? 0.f : __builtin_amdgcn_exp2f(x[r] - m_new);
+          l_run[qb] += s[qb][r];
+        }
+        m_run[qb] = m_new;
+#pragma unroll
+        for (int hd = 0; hd < HD; ++hd)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) o[qb][hd][e] *= alpha;
+      }
+      // A key that a row does not see must not reach it: a zero probability
+      // times an infinity or NaN would. Where an edge tile holds such a value,
+      // its products are formed one by one, of visible keys only.
+      bool odd = false;
+      if (edge) {
+        float z = 0.f;
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+          for (int hd = 0; hd < HD; ++hd)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) z = fmaf(vr[r][hd][e], 0.f, z);
+        odd = __any(z != z);
+      }
+      if (odd) {
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb)
+          for (int sg = 0; sg < 4; ++sg)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+              const float pk = __shfl(s[qb][r], 16 * sg + l16);
+              if (!((uint32_t)__shfl((int)vis[qb], 16 * sg + l16) >> r & 1u)) continue;
+              const float* vp = vb + (size_t)(k0 + 4 * sg + r) * kvs + 16 * lg;
+#pragma unroll
+              for (int hd = 0; hd < HD; ++hd)
+#pragma unroll
+                for (int x = 0; x < 4; ++x)
+#pragma unroll
+                  for (int e = 0; e < 4; ++e) o[qb][hd][e][x] = fmaf(pk, vp[64 * hd + 4 * x + e], o[qb][hd][e][x]);
+            }
+      } else {
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+          for (int hd = 0; hd < HD; ++hd)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+              for (int qb = 0; qb < QB; ++qb)
+                o[qb][hd][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(vr[r][hd][e], s[qb][r], o[qb][hd][e], 0, 0, 0);
+      }
     }
-  }
-  if (q_ok) {
-    const float inv = (l_run > 0.f) ? p.out_scale / l_run : 0.f;
-    const size_t obase = ((size_t)(seq0 + qi) * p.Hq + h) * D;
+    // the waves' parts of one row block at a time, added in wave order
 #pragma unroll
-    for (int d = 0; d < D; ++d) store_out<OUT>(p.o, obase + d, acc[d] * inv);
+    for (int qb = 0; qb < QB; ++qb) {
+      const float lw = sum_xor32(sum_xor16(l_run[qb]));
+      if (lg == 0) {
+        msh[w][l16] = m_run[qb];
+        lsh[w][l16] = lw;
+      }
+#pragma unroll
+      for (int hd = 0; hd < HD; ++hd)
+#pragma unroll
+        for (int x = 0; x < 4; ++x)
+          *reinterpret_cast<f32x4*>(&osh[w][l16][64 * hd + 16 * lg + 4 * x]) =
+              f32x4{o[qb][hd][0][x], o[qb][hd][1][x], o[qb][hd][2][x], o[qb][hd][3][x]};
+      __syncthreads();
+      const int row = tid / (D / 4), d4 = tid % (D / 4) * 4, qi = m0 + 16 * qb + row;
+      if (row < 16 && qi < len) {
+        float m = msh[0][row];
+#pragma unroll
+        for (int x = 1; x < NW; ++x) m = fmaxf(m, msh[x][row]);
+        f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+        float l = 0.f;
+#pragma unroll
+        for (int x = 0; x < NW; ++x) {
+          if (msh[x][row] == -INFINITY && lsh[x][row] == 0.f) continue;  // a wave without a visible key
+          const float f = __builtin_amdgcn_exp2f(msh[x][row] - m);
+          l = fmaf(lsh[x][row], f, l);
+          const f32x4 ox = *reinterpret_cast<const f32x4*>(&osh[x][row][d4]);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) sum[e] = fmaf(ox[e], f, sum[e]);
+        }
+        const float inv = (l > 0.f) ? p.out_scale / l : 0.f;
+        const size_t ob = ((size_t)(seq0 + qi) * p.Hq + h) * D + d4;
+        sum *= inv;
+        if (OUT == LITEVLM_F32) {
+          *reinterpret_cast<f32x4*>(static_cast<float*>(p.o) + ob) = sum;
+        } else {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) store_out<OUT>(p.o, ob + e, sum[e]);
+        }
+      }
+      __syncthreads();  // the next block's parts take the same LDS rows
+    }
   }
 }
+static_assert(16 * (128 / 4) <= 64 * kF32Waves, "one 16-byte piece of a row block per thread");
 
 template <int D, bool CAUSAL, int OUT>
 static void launch_typed(const AttnArgs& a, AttnParams& p, hipStream_t stream) {
@@ -1110,17 +1251,30 @@ static void launch_typed(const AttnArgs& a, AttnParams& p, hipStream_t stream) {
     hipLaunchKernelGGL((attn_bf16_pipe_kernel<D, CAUSAL, OUT>), dim3(8 * p.per_xcd), dim3(256), 0, stream, p);
     return;
   }
-  const int bm = a.in_dtype == LITEVLM_F32 ? 64 : 128;
+  if (a.in_dtype == LITEVLM_F32) {
+    // One block of 16 rows a workgroup until that gives every CU two
+    // workgroups; then two blocks share the key and value operands (half the L2
+    // reads per product). Keys go to the waves alike in both, so a row's result
+    // does not depend on the bound.
+    const bool one = (long long)((a.max_seqlen + 15) / 16) * a.Hq * a.B <= 2LL * 256;
+    const int bm32 = one ? 16 : 32;
+    p.n_mtiles = (a.max_seqlen + bm32 - 1) / bm32;
+    p.n_work = p.n_mtiles * a.Hq * a.B;
+    p.per_xcd = (p.n_work + 7) / 8;
+    const dim3 g32((unsigned)std::min(8 * p.per_xcd, 1 << 22));  // a multiple of 8: L % 8 stays the XCD
+    if (one) hipLaunchKernelGGL((attn_fwd_f32_kernel<D, CAUSAL, OUT, 1>), g32, dim3(64 * kF32Waves), 0, stream, p);
+    else hipLaunchKernelGGL((attn_fwd_f32_kernel<D, CAUSAL, OUT, 2>), g32, dim3(64 * kF32Waves), 0, stream, p);
+    return;
+  }
+  const int bm = 128;
   p.n_mtiles = (a.max_seqlen + bm - 1) / bm;
   p.n_work = p.n_mtiles * a.Hq * a.B;
   p.per_xcd = (p.n_work + 7) / 8;
   const dim3 grid(8 * p.per_xcd);
   if (a.in_dtype == LITEVLM_BF16)
     hipLaunchKernelGGL((attn_bf16_kernel<D, CAUSAL, OUT>), grid, dim3(256), 0, stream, p);
-  else if (a.in_dtype == LITEVLM_FP8_E4M3)
-    hipLaunchKernelGGL((attn_fp8_kernel<D, CAUSAL, OUT>), grid, dim3(256), 0, stream, p);
   else
-    hipLaunchKernelGGL((attn_fwd_f32_kernel<D, CAUSAL, OUT>), grid, dim3(64), 0, stream, p);
+    hipLaunchKernelGGL((attn_fp8_kernel<D, CAUSAL, OUT>), grid, dim3(256), 0, stream, p);
 }
 
 template <int D>

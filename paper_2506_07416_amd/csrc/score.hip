@@ -317,8 +317,6 @@ struct RowTileBf16 {
   // each 16-lane group reads 16 rows x 1 piece: conflict-free
   __device__ __forceinline__ static int swz(int key) { return key & (NP - 1); }
 
-  static constexpr bool QSTAGE = true;  // query rows arrive through an LDS stage
-
   // k-step ks of lane half hl holds head dims 16*ks + 8*hl .. +7, read from a
   // staged row (pieces swizzled by swz of the row's index in the stage)
   __device__ __forceinline__ void init_lds(const uint8_t* stage, int srow, int lane) {
@@ -330,7 +328,7 @@ struct RowTileBf16 {
   }
 
   // s[nb][r] = S^T[key 32*nb + acc_row(r)][row lane % 32]
-  __device__ __forceinline__ void logits(const uint8_t* kl, f32x16 s[2], const QRows&, int, int) const {
+  __device__ __forceinline__ void logits(const uint8_t* kl, f32x16 s[2]) const {
 #pragma unroll
     for (int nb = 0; nb < 2; ++nb)
 #pragma unroll
@@ -370,8 +368,6 @@ struct RowTileFp8 {
   // rows 2i, 2i+1 fill 16 banks-groups between them: conflict-free
   __device__ __forceinline__ static int swz(int key) { return (key >> 1) & (NP - 1); }
 
-  static constexpr bool QSTAGE = true;  // query rows arrive through an LDS stage
-
   // k-step ks of lane half hl holds bytes 64*ks + 32*hl .. +31 of a staged row
   __device__ __forceinline__ void init_lds(const uint8_t* stage, int srow, int lane) {
     const int lq = lane & 31, hl = lane >> 5;
@@ -388,7 +384,7 @@ struct RowTileFp8 {
   }
 
   // s[nb][r] = S^T[key 32*nb + acc_row(r)][row lane % 32]
-  __device__ __forceinline__ void logits(const uint8_t* kl, f32x16 s[2], const QRows&, int, int) const {
+  __device__ __forceinline__ void logits(const uint8_t* kl, f32x16 s[2]) const {
 #pragma unroll
     for (int nb = 0; nb < 2; ++nb)
 #pragma unroll
@@ -409,29 +405,48 @@ struct RowTileFp8 {
 
 template <int D>
 struct RowTileF32 {
-  // Plain fp32 FMAs; fp32 inputs are only used at small sizes. Query rows are
-  // read from global memory, keys from the LDS tile (unswizzled).
+  // v_mfma_f32_32x32x2_f32: the piece of "k-step" ks and lane half hl holds
+  // head dims 8*ks + 4*hl .. +3, one per MFMA. The whole selection call, against
+  // FMAs on rows read from global memory once per product (both sweeps): 300
+  // visual tokens, 16 heads of 64 99 -> 37 us; 2 x 1024, 32/8 heads of 128 353 ->
+  // 74 us. At D = 128 some registers spill; one sum per logit spills less and takes
+  // 63 us, at a larger error (7.3e-8 of the scores against 5.8e-8 here, 6.6e-8 for
+  // the FMAs).
   static constexpr int RB = D * 4;
   static constexpr int NP = RB / 16;
+  static constexpr int KS = D / 8;
   static constexpr int TILE = KB * RB;
   static constexpr int NBUF = TILE >= 32768 ? 3 : 4;  // LDS budget of the 32 KB fp32 tiles
-  static constexpr bool QSTAGE = false;  // query rows are read from global memory in logits
-  __device__ __forceinline__ static int swz(int) { return 0; }
-  __device__ __forceinline__ void init_lds(const uint8_t*, int, int) {}
+  f32x4 q[KS];
+  uint32_t kbase;  // as in the bf16 tile
+  __device__ __forceinline__ static int swz(int key) { return key & (NP - 1); }
 
-  // row0: the wave's first query row
-  __device__ __forceinline__ void logits(const uint8_t* kl, f32x16 s[2], const QRows& qr, int row0, int lane) const {
+  __device__ __forceinline__ void init_lds(const uint8_t* stage, int srow, int lane) {
     const int lq = lane & 31, hl = lane >> 5;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks)
+      q[ks] = *reinterpret_cast<const f32x4*>(stage + srow * RB + ((2 * ks + hl) ^ swz(srow)) * 16);
+    kbase = lq * RB + (hl ^ swz(lq)) * 16;  // key 32*nb + lq adds 32*nb*RB
+  }
+
+  // The two halves of the head dims in sums of their own: half the roundings along each.
+  __device__ __forceinline__ void logits(const uint8_t* kl, f32x16 s[2]) const {
+    uint32_t kb = kbase;
+    asm volatile("" : "+v"(kb));
 #pragma unroll
     for (int nb = 0; nb < 2; ++nb)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int key = 32 * nb + acc_row(r, hl);
-        const float* qf = reinterpret_cast<const float*>(qr.row(row0 + lq));
-        const float* kf = reinterpret_cast<const float*>(kl + key * RB);
-        float acc = 0.f;
-        for (int dd = 0; dd < D; ++dd) acc = fmaf(qf[dd], kf[dd], acc);
-        s[nb][r] = acc;
+      for (int half = 0; half < 2; ++half) {
+        f32x16 t = {};
+#pragma unroll
+        for (int ks = half * KS / 2; ks < (half + 1) * KS / 2; ++ks) {
+          const f32x4 ka = *reinterpret_cast<const f32x4*>(kl + nb * 32 * RB + (kb ^ (32u * ks)));
+#pragma unroll
+          for (int e = 0; e < 4; ++e) t = __builtin_amdgcn_mfma_f32_32x32x2f32(ka[e], q[ks][e], t, 0, 0, 0);
+          // at D = 128 the query rows leave registers for one step's keys only
+          if (D == 128) __builtin_amdgcn_sched_barrier(0);
+        }
+        s[nb] = half ? s[nb] + t : t;
       }
   }
 };
@@ -595,15 +610,15 @@ score_rowstats_kernel(ScoreDims d, const void* __restrict__ qv, const void* __re
   // where the rows fit), and each wave then reads its operand registers from
   // it. The keep bytes and flag words sit after the ring, inside the stage.
   constexpr int NPRE = Tile::NBUF < 3 ? Tile::NBUF - 1 : 2;  // key tiles in flight while the stage is in use
-  constexpr int QOFF = Tile::QSTAGE ? NPRE * Tile::TILE : Tile::NBUF * Tile::TILE;
-  constexpr int QROWS_MAX = Tile::QSTAGE ? (kLdsBytes - QOFF) / (32 * Tile::RB) * 32 : 32;
-  constexpr int QRR = Tile::QSTAGE ? (RBLK < QROWS_MAX ? RBLK : QROWS_MAX) : 1;
-  constexpr int QST = Tile::QSTAGE ? QRR * Tile::RB : 0;
-  constexpr int NQR = Tile::QSTAGE ? (RBLK + QRR - 1) / QRR : 0;
+  constexpr int QOFF = NPRE * Tile::TILE;
+  constexpr int QROWS_MAX = (kLdsBytes - QOFF) / (32 * Tile::RB) * 32;
+  constexpr int QRR = RBLK < QROWS_MAX ? RBLK : QROWS_MAX;
+  constexpr int QST = QRR * Tile::RB;
+  constexpr int NQR = (RBLK + QRR - 1) / QRR;
   constexpr int FOFF = Tile::NBUF * Tile::TILE;  // keep bytes, then flag words
   constexpr int FEND = FOFF + kMaxSplitTiles * KB + 2 * kSweepWaves * 8;
   constexpr int LDS_BYTES = FEND > QOFF + QST ? FEND : QOFF + QST;
-  static_assert(!Tile::QSTAGE || (QRR % 32 == 0 && QST % 1024 == 0), "stage rounds must hold whole waves and copies");
+  static_assert(QRR % 32 == 0 && QST % 1024 == 0, "stage rounds must hold whole waves and copies");
   static_assert(LDS_BYTES <= kLdsBytes, "sweep-1 LDS layout exceeds the workgroup limit");
   // One LDS object (key ring, query stage, keep bytes, flag words): with a
   // single object the compiler adds no vmcnt wait of its own before reads of
@@ -684,28 +699,26 @@ score_rowstats_kernel(ScoreDims d, const void* __restrict__ qv, const void* __re
   KeyPipe<Tile> pipe(lds, k + ((size_t)b * d.S * d.Hkv + g) * Tile::RB, (size_t)d.Hkv * Tile::RB, tile0, ntl,
                      d.S, w, lane, list, bal);
 #pragma unroll
-  for (int t = 0; t < (Tile::QSTAGE ? NPRE : Tile::NBUF - 1); ++t) pipe.issue(t);
-  if (Tile::QSTAGE) q_round(0);
+  for (int t = 0; t < NPRE; ++t) pipe.issue(t);
+  q_round(0);
   asm volatile("" ::: "memory");  // keep the copies ahead of the keep-byte loads
   uint8_t kf[kFlagsPer];
   ViewIn vin;
   if constexpr (VSEL) vin = view_load(d.vs.logit, d.vs.lexical, d.vs.N, b, lane);
   else load_keep_bytes(keep_row, tile0, d.V_full, w, lane, kf);
-  if (Tile::QSTAGE) {
-    wait_vmcnt<0>();  // round 0, the first key tiles and the keep bytes have landed
+  wait_vmcnt<0>();  // round 0, the first key tiles and the keep bytes have landed
+  __syncthreads();
+  if (wave_active && my_round == 0) tile.init_lds(qstage, srow, lane);
+  for (int round = 1; round < NQR; ++round) {
+    __syncthreads();  // every read of the previous round is done
+    q_round(round);
+    wait_vmcnt<0>();
     __syncthreads();
-    if (wave_active && my_round == 0) tile.init_lds(qstage, srow, lane);
-    for (int round = 1; round < NQR; ++round) {
-      __syncthreads();  // every read of the previous round is done
-      q_round(round);
-      wait_vmcnt<0>();
-      __syncthreads();
-      if (wave_active && my_round == round) tile.init_lds(qstage, srow, lane);
-    }
-    __syncthreads();  // every read of the stage is done: buffers 2.. may be filled
-#pragma unroll
-    for (int t = NPRE; t < Tile::NBUF - 1; ++t) pipe.issue(t);
+    if (wave_active && my_round == round) tile.init_lds(qstage, srow, lane);
   }
+  __syncthreads();  // every read of the stage is done: buffers 2.. may be filled
+#pragma unroll
+  for (int t = NPRE; t < Tile::NBUF - 1; ++t) pipe.issue(t);
   pipe.wait_for(0);
   __syncthreads();  // tile 0 and the keep bytes have landed
   if constexpr (VSEL) {
@@ -768,7 +781,9 @@ score_rowstats_kernel(ScoreDims d, const void* __restrict__ qv, const void* __re
   // statistics of tile t-1 and then forms the logits of tile t, keeping them
   // across the barrier. On each SIMD one group's VALU work overlaps the other
   // group's MFMAs.
-  const bool lag = (w & 4) != 0;
+  // The fp32 tiles, which spend nearly all of a step on MFMAs, keep no logits
+  // across steps (they have no registers left for them).
+  const bool lag = DT != LITEVLM_F32 && (w & 4) != 0;
   f32x16 s[2];
   for (int t = 0; t < ntl; ++t) {
     // the buffer of tile t+NBUF-1 was last read in step t-1
@@ -776,9 +791,9 @@ score_rowstats_kernel(ScoreDims d, const void* __restrict__ qv, const void* __re
     if (wave_active) {
       if (lag) {
         if (t > 0 && ((live >> (t - 1)) & 1ull)) stats(t - 1, s);
-        if ((live >> t) & 1ull) tile.logits(pipe.buf(t), s, qr, row0, lane);
+        if ((live >> t) & 1ull) tile.logits(pipe.buf(t), s);
       } else if ((live >> t) & 1ull) {
-        tile.logits(pipe.buf(t), s, qr, row0, lane);
+        tile.logits(pipe.buf(t), s);
         stats(t, s);
       }
     }
@@ -906,36 +921,47 @@ struct ColTileFp8 {
 
 template <int D>
 struct ColTileF32 {
-  // Plain fp32 FMAs; fp32 inputs are only used at small sizes. The lane's two
-  // keys are read from global memory, its 16 accumulator rows from LDS.
+  // v_mfma_f32_32x32x2_f32, pieces as in RowTileF32 (times there).
   static constexpr int RB = D * 4;
   static constexpr int NP = RB / 16;
-  const uint8_t* kbase;
-  size_t kstride;
-  int nvalid;
-  __device__ __forceinline__ static int qswz(int) { return 0; }
-  __device__ __forceinline__ void init(int) {}
+  static constexpr int KS = D / 8;
+  f32x4 kreg[2][KS];
+  uint32_t rbase;  // as in the bf16 tile
+  __device__ __forceinline__ static int qswz(int r) { return r & (NP - 1); }
 
-  __device__ __forceinline__ void load_keys(const uint8_t* kb_, size_t ks_, int nv, int) {
-    kbase = kb_;
-    kstride = ks_;
-    nvalid = nv;
+  __device__ __forceinline__ void init(int lane) {
+    const int lq = lane & 31, hl = lane >> 5;
+    rbase = lq * RB + (hl ^ qswz(lq)) * 16;
   }
 
-  __device__ __forceinline__ void logits(const uint8_t* buf, int lane, f32x16 s[2]) const {
+  __device__ __forceinline__ void load_keys(const uint8_t* kbase, size_t kstride, int nvalid, int lane) {
     const int lq = lane & 31, hl = lane >> 5;
 #pragma unroll
     for (int nb = 0; nb < 2; ++nb) {
-      const int key = nb * 32 + lq;
-      const float* kr = reinterpret_cast<const float*>(kbase + min(key, max(nvalid - 1, 0)) * kstride);
-      for (int r = 0; r < 16; ++r) {
-        const float* qf = reinterpret_cast<const float*>(buf + acc_row(r, hl) * RB);
-        float acc = 0.f;
-        if (key < nvalid)
-          for (int dd = 0; dd < D; ++dd) acc = fmaf(qf[dd], kr[dd], acc);
-        s[nb][r] = acc;
-      }
+      const int key = min(nb * 32 + lq, max(nvalid - 1, 0));
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks)
+        kreg[nb][ks] = *reinterpret_cast<const f32x4*>(kbase + key * kstride + (ks * 8 + 4 * hl) * 4);
     }
+  }
+
+  // the two halves of the head dims in sums of their own, as in RowTileF32
+  __device__ __forceinline__ void logits(const uint8_t* buf, int, f32x16 s[2]) const {
+    uint32_t rb = rbase;
+    asm volatile("" : "+v"(rb));
+#pragma unroll
+    for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+      for (int half = 0; half < 2; ++half) {
+        f32x16 t = {};
+#pragma unroll
+        for (int ks = half * KS / 2; ks < (half + 1) * KS / 2; ++ks) {
+          const f32x4 qa = *reinterpret_cast<const f32x4*>(buf + (rb ^ (32u * ks)));
+#pragma unroll
+          for (int e = 0; e < 4; ++e) t = __builtin_amdgcn_mfma_f32_32x32x2f32(qa[e], kreg[nb][ks][e], t, 0, 0, 0);
+        }
+        s[nb] = half ? s[nb] + t : t;
+      }
   }
 };
 

@@ -431,6 +431,8 @@ ROWS_CASES = [
     ("rows2-d64", dict(cfg=2, Tv=50, T=3, Hq=6, Hkv=3, D=64, keep_ratio=0.9), 2),
     ("rows1-fp8", dict(cfg=5, Tv=128, T=32), 1),
     ("rows1-f32", dict(cfg=1), 1),
+    # fp32 at D = 128 over several row blocks, ragged keys
+    ("rows150-f32-d128", dict(cfg=1, Tv=130, T=200, Hq=16, Hkv=4, D=128, B=2, keep_ratio=0.4), 150),
     ("rowsT-cfg2", dict(cfg=2, Tv=64, T=16), 16),
 ]
 
@@ -706,3 +708,39 @@ def test_attention_grid_bound_above_lengths(dtype):
     ref = oracle.prefill_attention(q64, k64, v64, cu, Hq, Hkv, 1 / math.sqrt(D))
     stats = check_attention(to_float64(outs[1]), ref, attn_kind(dtype), f"bound {dtype}")
     log(f"  grid bound 6272 vs {max(lens)}: bitwise equal; {stats}")
+
+
+@pytest.mark.parametrize("D,dtype_out", [(64, "f32"), (128, "f32"), (128, "bf16")])
+@pytest.mark.parametrize("lens", [[16, 1, 17, 0, 31, 32, 33], [300, 129, 128]])
+def test_attention_f32_row_blocks(lens, D, dtype_out):
+    """The fp32 kernel at the edges of its 16-row blocks and 16-key tiles, with one
+    and with two blocks to a workgroup (the second by a bound that makes the grid
+    large), bitwise alike; a value row of infinities reaches exactly the rows that
+    see it."""
+    Hq, Hkv = 4, 2
+    qb, kb, vb, _, cu = synth.random_attention_inputs(lens, Hq, Hkv, D, "f32", seed=77, peaked=True)
+    q, k, v = (to_device(x, "f32") for x in (qb, kb, vb))
+    cu_d = torch.from_numpy(cu).cuda()
+    odt = torch.float32 if dtype_out == "f32" else torch.bfloat16
+    bad = [int(cu[i]) + (3 * n) // 4 for i, n in enumerate(lens) if n > 1]
+    v_inf = v.clone()
+    v_inf[bad] = math.inf
+    got = []
+    for bound in (max(lens), 8192):
+        o = lv.prefill_attn(q, k, v, cu_d, bound, out_dtype=odt)
+        o_inf = lv.prefill_attn(q, k, v_inf, cu_d, bound, out_dtype=odt)
+        got.append((o, o_inf))
+    torch.cuda.synchronize()
+    (o, o_inf), (o2, o2_inf) = got
+    assert torch.equal(o.view(torch.uint8), o2.view(torch.uint8))
+    q64, k64, v64 = (oracle.litevlm.decode_stored(x, "f32", 1.0) for x in (qb, kb, vb))
+    ref = oracle.prefill_attention(q64, k64, v64, cu, Hq, Hkv, 1 / math.sqrt(D))
+    kind = attn_kind("f32" if dtype_out == "f32" else "bf16")
+    check_attention(to_float64(o), ref, kind, f"f32 D={D} lens={lens}")
+    sees = torch.zeros(int(cu[-1]), dtype=torch.bool, device="cuda")
+    for i, n in enumerate(lens):
+        if n > 1:
+            sees[int(cu[i]) + (3 * n) // 4:int(cu[i + 1])] = True
+    for x in (o_inf, o2_inf):
+        assert not torch.isfinite(x[sees]).any()
+        check_attention(to_float64(x[~sees]), ref[~sees.cpu().numpy()], kind, "rows before the infinities")
