@@ -15,15 +15,17 @@
 //   - a wave owns two column blocks that are rotary partners (elements d and
 //     d + D/2 of one head), so the rotation is lane-local in the accumulators.
 //
-// Tiling (the defaults below): a workgroup (4 waves) computes 128 rows x 128
-// output features; wave (wr, wc) holds rows 64*wr .. +64 and the column blocks
-// c0 and c0 + D/64. A and B tiles of 64 columns of the model width stream
-// global -> LDS directly (global_load_lds_dwordx4) through a double buffer
-// (66 KB, two workgroups per CU) into 128-byte rows whose 16-byte pieces are
-// XOR-swizzled so that operand reads are free of bank conflicts. Measured
-// alternatives (256-row or 256-feature tiles, 3- to 6-stage rings, 32-column
-// stages, four workgroups per CU with 32-column stages) were slower or equal on
-// both the batch-1 and the batch-8 shapes.
+// Bound: MFMA in principle (about 730 flop per HBM byte), in fact the copies of
+// the tiles from L2: without them the 256 x 256 loop takes 0.88 us a 64-column
+// stage, its MFMA time, with them 1.5 us. So a tile is as large as the shape
+// gives every CU one, and its rows are staged in whole 128-byte lines (64
+// columns; with half lines the 128 x 128 tile took 430 against 394 us at batch 8).
+// A workgroup is 4 waves (2 x 2), one wave per SIMD for the large tiles with the
+// accumulators in the AGPRs; a wave's share of the tile is then so large (128 x
+// 128) that its LDS reads stay below the LDS rate. Global -> LDS copies are
+// buffer loads (no vector arithmetic, half the address traffic) spread over the
+// MFMAs. Two wave groups in turns on a SIMD (8 waves, one reading LDS while the
+// other multiplies) took 380 us at batch 8 where this takes 361.
 //
 // Epilogue: the rotation angle is reduced to [-1/2, 1/2] turns in double and
 // taken by the hardware sine and cosine (which work in turns), and the rotated
@@ -37,27 +39,26 @@
 namespace litevlm {
 namespace {
 
-// Staging: 64 columns of the model width per stage, double buffered.
-constexpr int kKT = 64, kStages = 2;  // Dm % kKT == 0 (host check)
-constexpr int kPieces = kKT / 8;      // 16-byte pieces per staged row
-constexpr int kRowB = kKT * 2;        // bytes per staged row
+constexpr int kNW = 4, kTh = 64 * kNW;
 
-// Workgroup tile MT rows x NT features over NW waves; each wave holds 64 rows
-// (two 32-row blocks) and NT / (NW / (MT / 64)) features.
-template <int MT, int NT, int NW>
+// Workgroup tile MT rows x NT features over 4 waves (2 x 2), staged KT columns of
+// the model width at a time in a ring of R stages.
+template <int MT, int NT, int KT, int R_>
 struct TsmTile {
+  static constexpr int R = R_;
+  static constexpr int kPieces = KT / 8;  // 16-byte pieces per staged row
+  static constexpr int kRowB = KT * 2;    // bytes per staged row
   static constexpr int kAB = MT * kRowB;  // A tile bytes per stage
   static constexpr int kBB = NT * kRowB;  // B tile bytes per stage
   static constexpr int kStageB = kAB + kBB;
-  static constexpr int kRingB = kStages * kStageB;
-  static constexpr int kLdsB =
-      kRingB + MT * 4 /* row factors */ + MT * 4 /* positions */ + 128 /* reductions */ + MT /* keep flags */;
-  static constexpr int kWgPerCu = (160 * 1024 / kLdsB) >= 2 ? 2 : 1;
-  static constexpr int kThreads = 64 * NW;
-  static constexpr int kNWR = MT / 64;       // waves along the rows
-  static constexpr int kNWC = NW / kNWR;     // waves along the features (share rows)
-  static constexpr int kCBW = NT / kNWC / 32;  // 32-feature blocks per wave
-  static_assert(kNWR * kNWC == NW && (kCBW == 2 || kCBW == 4), "tile shape");
+  static constexpr int kRingB = R * kStageB;
+  static constexpr int kLdsB = kRingB + MT * 4 /* row factors */ + MT * 4 /* positions */ + 128 /* reductions */ +
+                               MT /* keep flags */;
+  static constexpr int kWgPerCu = 2 * kLdsB <= 160 * 1024 ? 2 : 1;
+  static constexpr int kRB = MT / 64;   // 32-row blocks per wave
+  static constexpr int kCBW = NT / 64;  // 32-feature blocks per wave
+  static_assert(kRB % 2 == 0 && (kCBW == 2 || kCBW == 4), "tile shape");
+  static_assert(kLdsB <= 160 * 1024, "LDS of a workgroup");
 };
 
 struct TsmParams {
@@ -68,8 +69,8 @@ struct TsmParams {
   uint16_t* q;          // bf16 [B, S, Hq, D]
   uint16_t* k;          // bf16 [B, S, Hkv, D]
   int B, S, V_full, Dm, Hq, Hkv;
-  int mk, nk, mq, nq, gk, gq, per_xcd;  // gk, gq: key and query row tiles (B*mk, B*mq)
-  int compact;                          // deal the working key row tiles by rank (kMT = 256 only)
+  int mk, nk, mq, nq, gk, gq;           // gk, gq: key and query row tiles (B*mk, B*mq)
+  int compact;                          // leave out the key row tiles without a kept row
   float eps;
   double log2_theta;
 };
@@ -80,126 +81,98 @@ __device__ __forceinline__ void vm_wait() {
 }
 
 // XOR swizzle of a staged row's pieces. The LDS serves a 16-byte read for 16
-// lanes per cycle across 64 banks (256 bytes): the 16 consecutive rows such a
-// group reads must put their pieces in distinct 16-byte bank slots. A 256-byte
-// bank window holds 256 / (2*kKT) rows, so rows that share a window position
-// get distinct pieces.
-__device__ __forceinline__ int swz(int row) { return kPieces == 4 ? (row >> 2) & 3 : (row >> 1) & 7; }
+// lanes per cycle across 64 banks (256 bytes, 16 / PIECES staged rows): the 16
+// consecutive rows such a group reads must put their pieces in distinct 16-byte
+// bank slots.
+template <int PIECES>
+__device__ __forceinline__ int swz(int row) { return PIECES == 4 ? (row >> 2) & 3 : (row >> 1) & 7; }
 
 // Workgroup barrier that waits only for this wave's LDS operations: the
 // __syncthreads fence would also wait for every direct copy still in flight,
 // which would drain the ring each stage.
 __device__ __forceinline__ void ring_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
-__device__ __forceinline__ int acc_row(int r, int hl) { return 8 * (r >> 2) + 4 * hl + (r & 3); }
-
 typedef uint32_t u32x4v __attribute__((ext_vector_type(4)));
-typedef __bf16 bf16x2v __attribute__((ext_vector_type(2)));
+typedef short s16x4v __attribute__((ext_vector_type(4)));
 
-// x.lo*y.lo + x.hi*y.hi + c on packed bf16 pairs (fp32 accumulate).
-__device__ __forceinline__ float dot2_bf16(uint32_t x, uint32_t y, float c) {
-  return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2v, x), __builtin_bit_cast(bf16x2v, y), c, false);
-}
+// Sum of the bytes of x plus c.
+__device__ __forceinline__ uint32_t sum_bytes(uint32_t x, uint32_t c) { return __builtin_amdgcn_sad_u8(x, 0u, c); }
 
-template <int D, int MT, int NT, int NW>
-__global__ __launch_bounds__(64 * NW, (TsmTile<MT, NT, NW>::kWgPerCu)) void tsm_proj_kernel(TsmParams p) {
-  using Tl = TsmTile<MT, NT, NW>;
+template <int D, int MT, int NT, int KT, int R>
+__global__ __launch_bounds__(kTh, (TsmTile<MT, NT, KT, R>::kWgPerCu)) void tsm_proj_kernel(TsmParams p) {
+#ifdef __HIP_DEVICE_COMPILE__  // the buffer descriptors are no host types
+  using Tl = TsmTile<MT, NT, KT, R>;
+  constexpr int kPieces = Tl::kPieces, kRowB = Tl::kRowB;
   constexpr int kMT = MT, kNT = NT, kAB = Tl::kAB, kBB = Tl::kBB, kStageB = Tl::kStageB, kRingB = Tl::kRingB;
-  constexpr int kTh = Tl::kThreads, NWR = Tl::kNWR, NWC = Tl::kNWC;
+  constexpr int NW = kNW, NWR = 2;
   constexpr int PB = D / 64;     // column-block distance of rotary partners
-  constexpr int RB = 2;          // 32-row blocks per wave
+  constexpr int RB = Tl::kRB;    // 32-row blocks per wave
   constexpr int CBW = Tl::kCBW;  // 32-column blocks per wave
   __shared__ __attribute__((aligned(1024))) uint8_t lds[Tl::kLdsB];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  // ---- work item. The items are the key row tiles with each of their feature
+  // tiles, then the query row tiles with theirs; an XCD takes a contiguous range
+  // (a row tile's feature tiles share its rows of x in that L2), the ranges
+  // equal to within one item.
   bool isq;
   int b, mt, nt;
-  if (MT == 256 && p.compact) {
-    // Only the key row tiles that hold a kept row produce anything. Every
-    // workgroup finds them from the keep bytes (one wave per tile in turn,
-    // four bytes a lane) and deals them, with their feature tiles, to the
-    // XCDs round robin by rank: each XCD gets the same number of working
-    // items whatever the dropped views, and a row tile's feature tiles stay on
-    // one XCD (they share its rows of x in that L2). The query items follow,
-    // continuing the rotation. The flags go into the ring, unused until the
-    // stage copies start.
-    uint8_t* gf = lds;
-    for (int g0 = 0; g0 < p.gk; g0 += 8 * NW) {
-      uint32_t any8 = 0;
-      uint8_t kb[8][4];
+  {
+    int nwork = p.gk;  // key row tiles to compute
+    if (p.compact) {
+      // Only those that hold a kept row: every workgroup finds them from the
+      // keep bytes, 16 at a time (host check: S and the mask are multiples of 16),
+      // all in flight together. The flags go into the ring, unused until the
+      // stage copies start.
+      for (int g = tid; g < p.gk; g += kTh) lds[g] = 0;
+      __syncthreads();
+      const uint4* k16 = reinterpret_cast<const uint4*>(p.keep);
+      const int n16 = p.B * (p.S / 16), s16 = p.S / 16;
+      constexpr int U = 16;
+      for (int p0 = 0; p0 < n16; p0 += U * kTh) {
+        uint4 u[U];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const int g = g0 + u * NW + w;
-        const int gb = g / p.mk, r0 = (g % p.mk) * kMT;
+        for (int i = 0; i < U; ++i) u[i] = k16[min(p0 + i * kTh + tid, n16 - 1)];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int r = r0 + lane + 64 * e;  // kMT = 256 rows: 64 lanes x 4
-          kb[u][e] = (g < p.gk && r < p.S) ? p.keep[(size_t)gb * p.S + r] : 0;
+        for (int i = 0; i < U; ++i) {
+          const int pc = min(p0 + i * kTh + tid, n16 - 1), pb = pc / s16;
+          if ((u[i].x | u[i].y | u[i].z | u[i].w) != 0u) lds[pb * p.mk + (pc - pb * s16) / (kMT / 16)] = 1;
         }
       }
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const bool kept = (kb[u][0] | kb[u][1] | kb[u][2] | kb[u][3]) != 0;
-        any8 |= (__ballot(kept) != 0ull ? 1u : 0u) << u;
-      }
-      if (lane == 0) {
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-          const int g = g0 + u * NW + w;
-          if (g < p.gk) gf[g] = (uint8_t)((any8 >> u) & 1u);
+      __syncthreads();
+      nwork = 0;
+      for (int c0 = 0; c0 < p.gk; c0 += 64) nwork += __popcll(__ballot(c0 + lane < p.gk && lds[c0 + lane] != 0));
+    }
+    const int total = nwork * p.nk + p.gq * p.nq;
+    const int x = blockIdx.x & 7;
+    const int i0 = (int)(((int64_t)x * total) >> 3), i1 = (int)(((int64_t)(x + 1) * total) >> 3);
+    int item = i0 + (int)(blockIdx.x >> 3);
+    if (item >= i1) return;
+    isq = item >= nwork * p.nk;
+    if (isq) item -= nwork * p.nk;
+    const int per = isq ? p.nq : p.nk, mm = isq ? p.mq : p.mk;
+    int grp = item / per;
+    nt = item - grp * per;
+    if (p.compact) {
+      if (!isq) {
+        // the working tile of rank grp (every wave finds the same)
+        const int rk = grp;
+        int seen = 0;
+        for (int c0 = 0; c0 < p.gk; c0 += 64) {
+          const bool f = c0 + lane < p.gk && lds[c0 + lane] != 0;
+          const uint64_t m = __ballot(f);
+          const int cnt = __popcll(m);
+          if (rk >= seen && rk < seen + cnt) {
+            const int before = __popcll(m & ((1ull << lane) - 1ull));
+            const uint64_t sel = __ballot(f && before == rk - seen);
+            grp = c0 + __ffsll((unsigned long long)sel) - 1;
+          }
+          seen += cnt;
         }
       }
+      __syncthreads();  // every wave has read the flags: the ring may be filled
     }
-    __syncthreads();
-    // the working tile of rank x + 8*(j / nk), and the number of working tiles
-    // (every wave computes the same values)
-    const int x = blockIdx.x & 7, j = blockIdx.x >> 3;
-    const int rk = x + 8 * (j / p.nk);
-    int nwork = 0, grp = 0;
-    for (int c0 = 0; c0 < p.gk; c0 += 64) {
-      const bool f = c0 + lane < p.gk && gf[c0 + lane] != 0;
-      const uint64_t m = __ballot(f);
-      const int cnt = __popcll(m);
-      if (rk >= nwork && rk < nwork + cnt) {
-        const int before = __popcll(m & ((1ull << lane) - 1ull));
-        const uint64_t sel = __ballot(f && before == rk - nwork);
-        grp = c0 + __ffsll((unsigned long long)sel) - 1;
-      }
-      nwork += cnt;
-    }
-    const int ck = nwork > x ? (nwork - x + 7) / 8 : 0;  // working key tiles of this XCD
-    if (j < ck * p.nk) {
-      isq = false;
-      b = grp / p.mk;
-      mt = grp % p.mk;
-      nt = j % p.nk;
-    } else {
-      const int qi = (x - nwork % 8 + 8) % 8 + 8 * (j - ck * p.nk);
-      if (qi >= p.gq * p.nq) return;
-      isq = true;
-      b = qi / (p.mq * p.nq);
-      const int r = qi % (p.mq * p.nq);
-      mt = r / p.nq;
-      nt = r % p.nq;
-    }
-  } else {
-    // an XCD takes a contiguous item range
-    const int item = (blockIdx.x & 7) * p.per_xcd + (blockIdx.x >> 3);
-    const int n_k_items = p.gk * p.nk;
-    if (item >= n_k_items + p.gq * p.nq) return;
-    if (item < n_k_items) {
-      isq = false;
-      b = item / (p.mk * p.nk);
-      const int r = item % (p.mk * p.nk);
-      mt = r / p.nk;
-      nt = r % p.nk;
-    } else {
-      const int jq = item - n_k_items;
-      isq = true;
-      b = jq / (p.mq * p.nq);
-      const int r = jq % (p.mq * p.nq);
-      mt = r / p.nq;
-      nt = r % p.nq;
-    }
+    b = grp / mm;
+    mt = grp - b * mm;
   }
   const int row0 = (isq ? p.V_full : 0) + mt * kMT;  // first row of the tile within the sample
   const int nrows = min(kMT, p.S - row0);
@@ -215,12 +188,70 @@ __global__ __launch_bounds__(64 * NW, (TsmTile<MT, NT, NW>::kWgPerCu)) void tsm_
 
   const int wr = w % NWR, wc = w / NWR, hl = lane >> 5, l32 = lane & 31;
 
+  // ---- copies of a stage (fixed per-lane sources): copy j of a wave fills LDS
+  // pieces (w + 4j)*64 + lane of the A (resp. B) tile
+  constexpr int CA = kAB / (1024 * NW), CB = kBB / (1024 * NW), CS = CA + CB;  // copies per thread and stage
+  static_assert(CA % 2 == 0 && CB % 2 == 0 && CS * (R - 1) <= 63, "copies in halves, vmcnt range");
+  const uint8_t* xt = p.x + ((size_t)b * p.S + row0) * Dm * 2;  // the tile's first row
+  const uint8_t* wt = W + (size_t)n0 * Dm * 2;                  // the tile's first feature
+  uint32_t asrc[CA], bsrc[CB];
+#pragma unroll
+  for (int j = 0; j < CA; ++j) {
+    const int slot = (w + NW * j) * 64 + lane;
+    const int row = slot / kPieces, logical = (slot % kPieces) ^ swz<kPieces>(row);
+    asrc[j] = (uint32_t)(min(row, nrows - 1) * Dm + logical * 8) * 2;  // < 256 * 65536 * 2
+  }
+#pragma unroll
+  for (int j = 0; j < CB; ++j) {
+    const int slot = (w + NW * j) * 64 + lane;
+    const int row = slot / kPieces, logical = (slot % kPieces) ^ swz<kPieces>(row);
+    bsrc[j] = (uint32_t)(row * Dm + logical * 8) * 2;
+  }
+  const uint32_t lds_w = __builtin_amdgcn_readfirstlane((uint32_t)w * 1024u);
+  const int nK = Dm / KT;
+  // buffer form: a 32-bit offset per lane and the stage's column in a scalar, so a
+  // copy costs no vector arithmetic and half the address traffic
+  const auto xr = __builtin_amdgcn_make_buffer_rsrc((void*)xt, 0, nrows * Dm * 2, 0x00027000);
+  const auto wr_ = __builtin_amdgcn_make_buffer_rsrc((void*)wt, 0, kNT * Dm * 2, 0x00027000);
+  // copies of stage s (past the end, the last stage's again, into bytes that
+  // nothing reads: the loop stays one block of code) in two halves
+  auto copy_half = [&](int s, uint32_t slot, int half) __attribute__((always_inline)) {
+    const int col = min(s, nK - 1) * kRowB;
+    uint8_t* st = lds + slot + lds_w;
+#pragma unroll
+    for (int j = half * CA / 2; j < (half + 1) * CA / 2; ++j)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(xr, (__attribute__((address_space(3))) void*)(st + NW * j * 1024), 16,
+                                               asrc[j], col, 0, 0);
+#pragma unroll
+    for (int j = half * CB / 2; j < (half + 1) * CB / 2; ++j)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(wr_, (__attribute__((address_space(3))) void*)(st + kAB + NW * j * 1024),
+                                               16, bsrc[j], col, 0, 0);
+  };
+  // the first stages are in flight while the positions are counted
+#pragma unroll
+  for (int s = 0; s < R; ++s) {
+    copy_half(s, s * kStageB, 0);
+    if (s < R - 1) copy_half(s, s * kStageB, 1);
+  }
+
   // ---- positions of the tile's rows in the patch-selected sequence
   {
     const uint8_t* kr = p.keep ? p.keep + (size_t)b * p.S : nullptr;
+    // kept rows before the tile, 16 bytes a load between an unaligned head and tail
     int cnt = 0;
-    if (kr)
-      for (int j = tid; j < row0; j += kTh) cnt += kr[j];
+    if (kr) {
+      const int head = min(row0, (int)((16 - (reinterpret_cast<uintptr_t>(kr) & 15)) & 15));
+      const int n16 = (row0 - head) / 16, tail = head + 16 * n16;
+      const uint4* k16 = reinterpret_cast<const uint4*>(kr + head);
+      uint32_t c = 0;
+      if (tid < head) c += kr[tid];
+      if (tid < row0 - tail) c += kr[tail + tid];
+      for (int j = tid; j < n16; j += kTh) {
+        const uint4 u = k16[j];
+        c = sum_bytes(u.w, sum_bytes(u.z, sum_bytes(u.y, sum_bytes(u.x, c))));
+      }
+      cnt = (int)c;
+    }
 #pragma unroll
     for (int x = 1; x < kWave; x <<= 1) cnt += __shfl_xor(cnt, x, kWave);
     if (lane == 0) red[w] = cnt;
@@ -262,26 +293,17 @@ __global__ __launch_bounds__(64 * NW, (TsmTile<MT, NT, NW>::kWgPerCu)) void tsm_
   // keys of dropped views are never scored
   if (!isq && p.keep) {
     __syncthreads();
-    if (red[2 * NW] == 0) return;
+    if (red[2 * NW] == 0) {
+      vm_wait<0>();  // the copies into LDS land before the workgroup ends
+      return;
+    }
   }
 
-  // ---- per-lane copy sources (fixed) and operand offsets (fixed)
-  // copy j of a wave fills LDS pieces (w + 4j)*64 + lane of the A (resp. B) tile
-  constexpr int CA = kAB / (1024 * NW), CB = kBB / (1024 * NW);  // copies per thread per stage
-  size_t asrc[CA], bsrc[CB];
+  // ---- operand offsets: row (or feature) l32 of a 32-row block, piece 2*ks + hl
+  constexpr int KS = KT / 16;  // k16 steps per stage
+  uint32_t off[KS];
 #pragma unroll
-  for (int j = 0; j < CA; ++j) {
-    const int slot = (w + NW * j) * 64 + lane;
-    const int row = slot / kPieces, logical = (slot % kPieces) ^ swz(row);
-    asrc[j] = ((size_t)((size_t)b * p.S + row0 + min(row, nrows - 1)) * Dm + logical * 8) * 2;
-  }
-#pragma unroll
-  for (int j = 0; j < CB; ++j) {
-    const int slot = (w + NW * j) * 64 + lane;
-    const int row = slot / kPieces, logical = (slot % kPieces) ^ swz(row);
-    bsrc[j] = ((size_t)(n0 + row) * Dm + logical * 8) * 2;
-  }
-  const uint32_t lds_w = __builtin_amdgcn_readfirstlane((uint32_t)w * 1024u);
+  for (int ks = 0; ks < KS; ++ks) off[ks] = l32 * kRowB + (((2 * ks + hl) ^ swz<kPieces>(l32)) * 16);
   // this wave's column blocks: rotary partners (blocks PB apart) always together
   int cbl[CBW];
   if constexpr (CBW == 4) {
@@ -291,36 +313,15 @@ __global__ __launch_bounds__(64 * NW, (TsmTile<MT, NT, NW>::kWgPerCu)) void tsm_
     cbl[0] = (D == 128) ? wc : 2 * wc;
     cbl[1] = cbl[0] + PB;
   }
-  constexpr int KS = kKT / 16;          // k16 steps per stage
-  uint32_t aoff[RB][KS], boff[CBW][KS];  // [block][k16 step]
-#pragma unroll
-  for (int ks = 0; ks < KS; ++ks) {
-    const int logical = 2 * ks + hl;
-#pragma unroll
-    for (int rb = 0; rb < RB; ++rb) {
-      const int row = 64 * wr + 32 * rb + l32;
-      aoff[rb][ks] = row * kRowB + ((logical ^ swz(row)) * 16);
-    }
-#pragma unroll
-    for (int c = 0; c < CBW; ++c) {
-      const int nrow = 32 * cbl[c] + l32;
-      boff[c][ks] = kAB + nrow * kRowB + ((logical ^ swz(nrow)) * 16);
-    }
-  }
-
-  auto copy_stage = [&](int s) __attribute__((always_inline)) {
-    const size_t kb = (size_t)s * kKT * 2;
-    uint8_t* st = lds + (s % kStages) * kStageB;
-#pragma unroll
-    for (int j = 0; j < CA; ++j)
-      __builtin_amdgcn_global_load_lds((const void*)(p.x + asrc[j] + kb),
-                                       (__attribute__((address_space(3))) void*)(st + lds_w + NW * j * 1024), 16, 0, 0);
-#pragma unroll
-    for (int j = 0; j < CB; ++j)
-      __builtin_amdgcn_global_load_lds((const void*)(W + bsrc[j] + kb),
-                                       (__attribute__((address_space(3))) void*)(st + kAB + lds_w + NW * j * 1024), 16,
-                                       0, 0);
-  };
+  // The two waves of a row half take its 32-row blocks in another order (the second
+  // begins with the upper half), so that each sums the squares of its own first
+  // RB / 2 blocks without a branch.
+  constexpr int HB = RB / 2;
+  auto row_block = [&](int rb) { return wr * RB + (rb < HB ? rb + wc * HB : rb - wc * HB); };
+  const uint32_t a_lo = __builtin_amdgcn_readfirstlane((uint32_t)row_block(0) * 32u * kRowB);
+  const uint32_t a_hi = __builtin_amdgcn_readfirstlane((uint32_t)row_block(HB) * 32u * kRowB);
+  const uint32_t b0 = __builtin_amdgcn_readfirstlane((uint32_t)(kAB + cbl[0] * 32 * kRowB));
+  constexpr int kCStep = (CBW == 2 ? PB : 1) * 32 * kRowB;  // bytes between the wave's column blocks
 
   f32x16 acc[RB][CBW];
 #pragma unroll
@@ -329,69 +330,90 @@ __global__ __launch_bounds__(64 * NW, (TsmTile<MT, NT, NW>::kWgPerCu)) void tsm_
     for (int c = 0; c < CBW; ++c)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[rb][c][r] = 0.f;
-  float ssq[RB];
+  float ssq[HB][2];
 #pragma unroll
-  for (int rb = 0; rb < RB; ++rb) ssq[rb] = 0.f;
+  for (int rb = 0; rb < HB; ++rb) ssq[rb][0] = ssq[rb][1] = 0.f;
 
-  const int nK = Dm / kKT;
-  constexpr int CS = CA + CB;  // copies per thread per stage
-  static_assert(CS * (kStages - 2) <= 63 && kStages >= 2 && kStages <= 6, "vmcnt range");
-  for (int s = 0; s < kStages - 1 && s < nK; ++s) copy_stage(s);
-  for (int s = 0; s < nK; ++s) {
-    // stage s has landed once at most the copies of the stages issued after it remain
-    const int later = min(nK - 1, s + kStages - 2) - s;
-    if (later >= 4) vm_wait<4 * CS>();
-    else if (later == 3) vm_wait<3 * CS>();
-    else if (later == 2) vm_wait<2 * CS>();
-    else if (later == 1) vm_wait<CS>();
-    else vm_wait<0>();
-    ring_barrier();  // every wave's copies of stage s are visible; ring slot (s-1)%kStages is free
-    if (s + kStages - 1 < nK) copy_stage(s + kStages - 1);
-    const uint8_t* st = lds + (s % kStages) * kStageB;
+  // One wave per SIMD. The operands of a k16 step are read while the step before
+  // it multiplies. One barrier a stage, before its last step: by then every wave
+  // holds its last operands of the stage, so its slot is free, and the next
+  // stage has landed, so its first operands can be read. A stage's copies are
+  // spread over the MFMAs of the two steps after its slot became free, R - 1
+  // stages ahead (issued together they hold up the MFMAs).
+  bf16x8 a[2][RB], bo[2][CBW];
+  auto read_step = [&](int set, uint32_t slot, int ks) __attribute__((always_inline)) {
+    const uint8_t* st = lds + slot + off[ks];
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-      bf16x8 a[RB], bo[CBW];
+    for (int rb = 0; rb < RB; ++rb)
+      a[set][rb] = *reinterpret_cast<const bf16x8*>(st + (rb < HB ? a_lo : a_hi) + (rb % HB) * 32 * kRowB);
 #pragma unroll
-      for (int rb = 0; rb < RB; ++rb) a[rb] = *reinterpret_cast<const bf16x8*>(st + aoff[rb][ks]);
+    for (int c = 0; c < CBW; ++c) bo[set][c] = *reinterpret_cast<const bf16x8*>(st + b0 + c * kCStep);
+  };
+  auto multiply = [&](int set) __attribute__((always_inline)) {
 #pragma unroll
-      for (int c = 0; c < CBW; ++c) bo[c] = *reinterpret_cast<const bf16x8*>(st + boff[c][ks]);
+    for (int rb = 0; rb < RB; ++rb) {
 #pragma unroll
-      for (int rb = 0; rb < RB; ++rb)
+      for (int c = 0; c < CBW; ++c)
+        acc[rb][c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[set][rb], bo[set][c], acc[rb][c], 0, 0, 0);
+      // Row sums of squares of the A operands, two vector instructions per MFMA
+      // (they run beside it; the packed bf16 dot does not: 0.4 us a 64-column
+      // stage of the 256 x 256 tile)
+      if (rb < HB) {
+        const u32x4v u = __builtin_bit_cast(u32x4v, a[set][rb]);
 #pragma unroll
-        for (int c = 0; c < CBW; ++c)
-          acc[rb][c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[rb], bo[c], acc[rb][c], 0, 0, 0);
-      // Row sums of squares from the A operands on the packed bf16 dot unit. The
-      // two waves holding the same rows take alternate k16 steps, so every SIMD
-      // carries the same vector work.
-      if ((ks % NWC) == wc) {
-#pragma unroll
-        for (int rb = 0; rb < RB; ++rb) {
-          const u32x4v u = __builtin_bit_cast(u32x4v, a[rb]);
-#pragma unroll
-          for (int e = 0; e < 4; ++e) ssq[rb] = dot2_bf16(u[e], u[e], ssq[rb]);
+        for (int e = 0; e < 4; ++e) {
+          const float lo = __uint_as_float(u[e] << 16), hi = __uint_as_float(u[e] & 0xFFFF0000u);
+          ssq[rb][0] = fmaf(lo, lo, ssq[rb][0]);
+          ssq[rb][1] = fmaf(hi, hi, ssq[rb][1]);
         }
       }
     }
+  };
+  // MFMAs with the next step's LDS reads and the copies spread among them
+  auto interleave = [&]() __attribute__((always_inline)) {
+    constexpr int NM = RB * CBW;
+#pragma unroll
+    for (int i = 0; i < NM / 4; ++i) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);
+      }
+      __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  vm_wait<0>();
+  ring_barrier();
+  read_step(0, 0, 0);
+  uint32_t slot = 0, prev = (R - 1) * kStageB;  // slots of stages s and s - 1
+  for (int s = 0; s < nK; ++s) {
+    const uint32_t next = slot == (R - 1) * kStageB ? 0 : slot + kStageB;
+    copy_half(s + R - 1, prev, 1);
+#pragma unroll
+    for (int ks = 0; ks + 1 < KS; ++ks) {
+      read_step((ks + 1) & 1, slot, ks + 1);
+      multiply(ks & 1);
+      interleave();
+    }
+    vm_wait<(R - 2) * CS>();  // stage s + 1 has landed: R - 2 stages were issued after it
+    ring_barrier();
+    copy_half(s + R, slot, 0);
+    read_step(0, next, 0);  // past the last stage: bytes of another slot, not used
+    multiply(1);
+    interleave();
+    prev = slot;
+    slot = next;
   }
+  vm_wait<0>();  // the epilogue writes the ring
 
   // ---- epilogue: RMS factor per row, rotary embedding, bf16 store
-  // (the ring is free now: its first bytes hold the wc = 1 waves' partial sums)
-  float* part = reinterpret_cast<float*>(lds);  // [NWC][kMT]
   __syncthreads();
 #pragma unroll
-  for (int rb = 0; rb < RB; ++rb) {
-    const float tot = sum_xor32(ssq[rb]);
-    if (hl == 0) part[wc * kMT + 64 * wr + 32 * rb + l32] = tot;
-  }
-  __syncthreads();
-  if (wc == 0 && hl == 0) {
-#pragma unroll
-    for (int rb = 0; rb < RB; ++rb) {
-      const int row = 64 * wr + 32 * rb + l32;
-      float tot = 0.f;
-      for (int x = 0; x < NWC; ++x) tot += part[x * kMT + row];
-      rs[row] = 1.f / sqrtf(tot / (float)Dm + p.eps);
-    }
+  for (int rb = 0; rb < HB; ++rb) {
+    const float tot = sum_xor32(ssq[rb][0] + ssq[rb][1]);
+    if (hl == 0) rs[32 * row_block(rb) + l32] = 1.f / sqrtf(tot / (float)Dm + p.eps);
   }
   __syncthreads();
   // The rotated tile goes through the (now free) ring as bf16 rows of kNT
@@ -402,6 +424,26 @@ __global__ __launch_bounds__(64 * NW, (TsmTile<MT, NT, NW>::kWgPerCu)) void tsm_
   auto out_slot = [&](int row, int col) {
     return row * kOutRowB + ((((col * 2) >> 4) ^ (row & 7)) << 4) + ((col * 2) & 15);
   };
+  // Rows 4q .. 4q+3 of one column per lane, as 4-byte stores of two columns: the
+  // even lane of a pair takes rows 4q and 4q+2 of both, the odd lane the others.
+  const uint32_t pick = (lane & 1) ? 0x03020706u : 0x05040100u;
+  auto put4 = [&](int row4, int col, const float (&v)[4]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int e = 0; e < 4; e += 2) {
+      typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+      const uint32_t own = __builtin_bit_cast(uint32_t, bf16x2{(__bf16)v[e], (__bf16)v[e + 1]});
+      const uint32_t nb = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)own, 0xB1, 0xF, 0xF, false);  // lane ^ 1
+      *reinterpret_cast<uint32_t*>(lds + out_slot(row4 + e + (lane & 1), col & ~1)) =
+          __builtin_amdgcn_perm(nb, own, pick);
+    }
+  };
+  // sine and cosine of pos * theta^(-2d/D): the angle in turns, reduced to
+  // [-1/2, 1/2] in double; the hardware sine and cosine take turns
+  auto sincos_turns = [](double t, float& sn, float& cs) __attribute__((always_inline)) {
+    t -= rint(t);
+    sn = __builtin_amdgcn_sinf((float)t);
+    cs = __builtin_amdgcn_cosf((float)t);
+  };
   // rotary pairs of this wave's column list: slots c (a first-half block) and
   // cp (its partner, PB blocks on)
   auto rotate_pair = [&](auto ic) __attribute__((always_inline)) {
@@ -411,21 +453,39 @@ __global__ __launch_bounds__(64 * NW, (TsmTile<MT, NT, NW>::kWgPerCu)) void tsm_
     const int col = 32 * cbl[c] + l32;  // tile feature of the first-half element; its partner is D/2 on
     const int d = (32 * cbl[c]) % D + l32;  // element of the first half of its head (d < D/2)
     const double turns_per_pos = exp2(-(2.0 * d / D) * p.log2_theta) * 0.15915494309189535;  // / (2 pi)
+    float s1[3], c1[3];  // of 1, 2 and 3 positions
+#pragma unroll
+    for (int k = 0; k < 3; ++k) sincos_turns((k + 1) * turns_per_pos, s1[k], c1[k]);
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int row = 64 * wr + 32 * rb + acc_row(r, hl);
-        const float f = rs[row];
-        const float x1 = acc[rb][c][r] * f, x2 = acc[rb][cp][r] * f;
-        // angle pos * theta^(-2d/D) in turns, reduced to [-1/2, 1/2] in double;
-        // the hardware sine and cosine take turns
-        double t = (double)pos[row] * turns_per_pos;
-        t -= rint(t);
-        const float sn = __builtin_amdgcn_sinf((float)t), cs = __builtin_amdgcn_cosf((float)t);
-        *reinterpret_cast<uint16_t*>(lds + out_slot(row, col)) = f32_to_bf16_bits(x1 * cs - x2 * sn);
-        *reinterpret_cast<uint16_t*>(lds + out_slot(row, col + D / 2)) = f32_to_bf16_bits(x2 * cs + x1 * sn);
-        __builtin_amdgcn_sched_barrier(0);  // one row at a time: bounded live ranges
+      for (int q = 0; q < 4; ++q) {
+        const int row4 = 32 * row_block(rb) + 8 * q + 4 * hl;  // acc_row(4q .. 4q+3, hl)
+        const f32x4 f = *reinterpret_cast<const f32x4*>(rs + row4);
+        const i32x4 ps = *reinterpret_cast<const i32x4*>(pos + row4);
+        float sn[4], cs[4];
+        sincos_turns((double)ps[0] * turns_per_pos, sn[0], cs[0]);
+        // four rows in sequence (all but where tokens are dropped between them):
+        // the angle sums instead of a sine, a cosine and a double reduction each
+        if (__all(ps[1] == ps[0] + 1 && ps[2] == ps[0] + 2 && ps[3] == ps[0] + 3)) {
+#pragma unroll
+          for (int e = 1; e < 4; ++e) {
+            sn[e] = fmaf(sn[0], c1[e - 1], cs[0] * s1[e - 1]);
+            cs[e] = fmaf(cs[0], c1[e - 1], -(sn[0] * s1[e - 1]));
+          }
+        } else {
+#pragma unroll
+          for (int e = 1; e < 4; ++e) sincos_turns((double)ps[e] * turns_per_pos, sn[e], cs[e]);
+        }
+        float y1[4], y2[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float x1 = acc[rb][c][4 * q + e] * f[e], x2 = acc[rb][cp][4 * q + e] * f[e];
+          y1[e] = x1 * cs[e] - x2 * sn[e];
+          y2[e] = x2 * cs[e] + x1 * sn[e];
+        }
+        put4(row4, col, y1);
+        put4(row4, col + D / 2, y2);
       }
   };
   rotate_pair(std::integral_constant<int, 0>{});
@@ -443,6 +503,7 @@ __global__ __launch_bounds__(64 * NW, (TsmTile<MT, NT, NW>::kWgPerCu)) void tsm_
       *reinterpret_cast<u32x4v*>(out + ((size_t)b * p.S + row0 + row) * H * D + n0 + 8 * pc) = v;
     }
   }
+#endif
 }
 
 // w_out[n, c] = bf16(w[n, c] * gamma[c]): the RMS normalisation gain folded
@@ -482,30 +543,35 @@ hipError_t launch_tsm_qk(const TsmArgs& a, hipStream_t stream) {
     p.gk = a.B * p.mk;
     p.gq = a.B * p.mq;
     p.compact = 0;
-    p.per_xcd = (p.gk * p.nk + p.gq * p.nq + 7) / 8;
-    return dim3(8 * p.per_xcd);
+    return dim3((unsigned)(8 * (((int64_t)p.gk * p.nk + (int64_t)p.gq * p.nq + 7) / 8)));
   };
-  // 256 x 256 tiles (8 waves, one workgroup per CU) halve the L2 traffic per
-  // flop; they are used when they still give every CU a workgroup.
-  const bool big = (a.Hkv * a.D) % 256 == 0 && (a.Hq * a.D) % 256 == 0 &&
-                   (int64_t)a.B * ((a.S + 255) / 256) * (a.Hkv * a.D / 256) >= 256;
-  if (big) {
-    dim3 grid = setup(256, 256);
-    // the dealing workgroups keep one flag byte per key row tile in the stage
-    // ring: longer batches take the contiguous ranges
-    if (a.token_keep && p.gk <= TsmTile<256, 256, 8>::kRingB) {
-      // at most (gk+7)/8 working key row tiles per XCD, and (gq*nq+7)/8 query items
-      p.compact = 1;
-      p.per_xcd = (p.gk + 7) / 8 * p.nk + (p.gq * p.nq + 7) / 8;
-      grid = dim3(8 * p.per_xcd);
-    }
-    if (a.D == 128) hipLaunchKernelGGL((tsm_proj_kernel<128, 256, 256, 8>), grid, dim3(512), 0, stream, p);
-    else hipLaunchKernelGGL((tsm_proj_kernel<64, 256, 256, 8>), grid, dim3(512), 0, stream, p);
-  } else {
-    const dim3 grid = setup(128, 128);
-    if (a.D == 128) hipLaunchKernelGGL((tsm_proj_kernel<128, 128, 128, 4>), grid, dim3(256), 0, stream, p);
-    else hipLaunchKernelGGL((tsm_proj_kernel<64, 128, 128, 4>), grid, dim3(256), 0, stream, p);
-  }
+  // Workgroups of a tile shape with every view kept (the host does not know the mask).
+  auto items = [&](int MT, int NT) {
+    return (int64_t)a.B * (((a.S + MT - 1) / MT) * (int64_t)(a.Hkv * a.D / NT) + ((T + MT - 1) / MT) * (int64_t)(a.Hq * a.D / NT));
+  };
+  const bool wide = (a.Hkv * a.D) % 256 == 0 && (a.Hq * a.D) % 256 == 0;
+  auto launch = [&](auto kern, int MT, int NT, int ring) {
+    const dim3 grid = setup(MT, NT);
+    // the dealing workgroups read the mask in 16-byte pieces and keep one flag
+    // byte per key row tile in the stage ring
+    p.compact = a.token_keep && a.S % 16 == 0 && (reinterpret_cast<uintptr_t>(a.token_keep) & 15) == 0 && p.gk <= ring;
+    hipLaunchKernelGGL(kern, grid, dim3(kTh), 0, stream, p);
+  };
+#define LITEVLM_TSM(MT, NT, KT, R)                                                                  \
+  (a.D == 128 ? launch(tsm_proj_kernel<128, MT, NT, KT, R>, MT, NT, TsmTile<MT, NT, KT, R>::kRingB) \
+              : launch(tsm_proj_kernel<64, MT, NT, KT, R>, MT, NT, TsmTile<MT, NT, KT, R>::kRingB))
+  // One 128 x 128 tile per CU or fewer: the smallest tile's K loop is the
+  // shortest chain, in 32-column stages four deep (1536 visual tokens, 32/8 heads,
+  // width 4096: 41 us against 54 in 128 x 256 tiles; 392 tokens, 16/8 heads,
+  // width 2048: 23 against 32). Else 256-feature tiles where the heads divide so,
+  // of 256 rows where these take no more rounds of the chip at twice the time each
+  // (two prompts of 6144 visual tokens: 119 against 130 us; one: 106 against 70;
+  // eight: 361 against 356).
+  if (items(128, 128) <= 256) LITEVLM_TSM(128, 128, 32, 4);
+  else if (!wide) LITEVLM_TSM(256, 128, 64, 3);
+  else if (2 * ((items(256, 256) + 255) / 256) <= (items(128, 256) + 255) / 256) LITEVLM_TSM(256, 256, 64, 2);
+  else LITEVLM_TSM(128, 256, 64, 3);
+#undef LITEVLM_TSM
   return hipGetLastError();
 }
 

@@ -72,6 +72,14 @@ def check(got, ref, what):
     # LITEVLM_MAX_BATCH samples: 256 key row tiles of 256, the tiles dealt by rank
     ("256 samples of 2 views x 48 + 16 text, GQA 4/2", dict(B=256, N=2, Tv=48, T=16, Hq=4, Hkv=2, D=128,
                                                            n_masked=(0, 1)), 256),
+    # the other tile shapes: 256 x 256 (the mask read 16 bytes at a time, or by row ranges where
+    # a row of it is no multiple of 16), 128 x 256, and 256 x 128 where no 256 features divide
+    ("256 x 256 tiles, D=128", dict(B=72, N=2, Tv=104, T=32, Hq=4, Hkv=2, D=128, n_masked=(0, 1)), 128),
+    ("256 x 256 tiles, D=64, odd rows", dict(B=72, N=2, Tv=100, T=33, Hq=8, Hkv=4, D=64, n_masked=(0, 1)), 64),
+    ("128 x 256 tiles, D=128, odd rows", dict(B=36, N=2, Tv=100, T=33, Hq=4, Hkv=2, D=128, n_masked=(0, 1)), 192),
+    ("128 x 256 tiles, D=64", dict(B=36, N=2, Tv=104, T=32, Hq=8, Hkv=4, D=64, n_masked=(0, 1)), 64),
+    ("256 x 128 tiles, D=128", dict(B=72, N=3, Tv=69, T=33, Hq=4, Hkv=1, D=128, n_masked=(0, 2)), 320),
+    ("256 x 128 tiles, D=64, odd rows", dict(B=72, N=2, Tv=101, T=33, Hq=8, Hkv=2, D=64, n_masked=(0, 1)), 64),
 ])
 def test_tsm_matches_oracle(name, over, Dm):
     case = synth.config_case(2, **over)
