@@ -233,14 +233,13 @@ attn_bf16_kernel(AttnParams p) {
     const bool full = k0 + BN <= len;
 #pragma unroll
     for (int j = 0; j < LI; ++j) {
-      // rows past the sequence end repeat its last key
-      const uint32_t fix = full ? 0u : (uint32_t)(min(k0 + ld_row[j], len - 1) - (k0 + ld_row[j])) * kvrow;
-      __builtin_amdgcn_global_load_lds((const void*)(kt + (ld_koff[j] + fix)),
-                                       (__attribute__((address_space(3))) void*)(kvl + BUF * TB + lds_w + NW * j * 1024),
-                                       16, 0, 0);
-      __builtin_amdgcn_global_load_lds((const void*)(vt + (ld_voff[j] + fix)),
-                                       (__attribute__((address_space(3))) void*)(kvl + (2 + BUF) * TB + lds_w + NW * j * 1024),
-                                       16, 0, 0);
+      // rows past the sequence end repeat its last key; buffer copies: the
+      // global form's 64-bit addresses cost 48 vector instructions in this loop
+      // (3200 tokens 89.6 -> 86.6 us, 6272 tokens 316 -> 305 us)
+      uint32_t fix = 0;
+      if (!full) fix = (uint32_t)(min(k0 + ld_row[j], len - 1) - (k0 + ld_row[j])) * kvrow;
+      copy16_to_lds(kt, BN * kvrow, ld_koff[j] + fix, 0, kvl + BUF * TB + lds_w + NW * j * 1024);
+      copy16_to_lds(vt, BN * kvrow, ld_voff[j] + fix, 0, kvl + (2 + BUF) * TB + lds_w + NW * j * 1024);
     }
   };
 

@@ -56,6 +56,18 @@ __device__ __forceinline__ float max_xor32(float x) { const float2 p = pair_xor3
 __device__ __forceinline__ float sum_xor16(float x) { const float2 p = pair_xor16(x); return p.x + p.y; }
 __device__ __forceinline__ float sum_xor32(float x) { const float2 p = pair_xor32(x); return p.x + p.y; }
 
+// Direct copy of 16 bytes a lane into LDS (lane l to dst + 16*l): from the
+// wave-uniform base + off (per lane) + soff (uniform); off + soff + 16 <= bytes. The
+// buffer form takes a 32-bit offset a lane, where the global form takes a 64-bit
+// address formed by vector arithmetic for every copy.
+__device__ __forceinline__ void copy16_to_lds(const uint8_t* base, uint32_t bytes, uint32_t off, uint32_t soff,
+                                              uint8_t* dst) {
+#ifdef __HIP_DEVICE_COMPILE__  // the descriptor is no host type
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(__builtin_amdgcn_make_buffer_rsrc((void*)base, 0, (int)bytes, 0x00027000),
+                                           (__attribute__((address_space(3))) void*)dst, 16, (int)off, (int)soff, 0, 0);
+#endif
+}
+
 template <int CTRL>
 __device__ __forceinline__ float dpp(float x) {
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xF, 0xF, false));

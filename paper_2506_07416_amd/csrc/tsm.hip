@@ -100,7 +100,6 @@ __device__ __forceinline__ uint32_t sum_bytes(uint32_t x, uint32_t c) { return _
 
 template <int D, int MT, int NT, int KT, int R>
 __global__ __launch_bounds__(kTh, (TsmTile<MT, NT, KT, R>::kWgPerCu)) void tsm_proj_kernel(TsmParams p) {
-#ifdef __HIP_DEVICE_COMPILE__  // the buffer descriptors are no host types
   using Tl = TsmTile<MT, NT, KT, R>;
   constexpr int kPieces = Tl::kPieces, kRowB = Tl::kRowB;
   constexpr int kMT = MT, kNT = NT, kAB = Tl::kAB, kBB = Tl::kBB, kStageB = Tl::kStageB, kRingB = Tl::kRingB;
@@ -209,10 +208,6 @@ __global__ __launch_bounds__(kTh, (TsmTile<MT, NT, KT, R>::kWgPerCu)) void tsm_p
   }
   const uint32_t lds_w = __builtin_amdgcn_readfirstlane((uint32_t)w * 1024u);
   const int nK = Dm / KT;
-  // buffer form: a 32-bit offset per lane and the stage's column in a scalar, so a
-  // copy costs no vector arithmetic and half the address traffic
-  const auto xr = __builtin_amdgcn_make_buffer_rsrc((void*)xt, 0, nrows * Dm * 2, 0x00027000);
-  const auto wr_ = __builtin_amdgcn_make_buffer_rsrc((void*)wt, 0, kNT * Dm * 2, 0x00027000);
   // copies of stage s (past the end, the last stage's again, into bytes that
   // nothing reads: the loop stays one block of code) in two halves
   auto copy_half = [&](int s, uint32_t slot, int half) __attribute__((always_inline)) {
@@ -220,12 +215,10 @@ __global__ __launch_bounds__(kTh, (TsmTile<MT, NT, KT, R>::kWgPerCu)) void tsm_p
     uint8_t* st = lds + slot + lds_w;
 #pragma unroll
     for (int j = half * CA / 2; j < (half + 1) * CA / 2; ++j)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(xr, (__attribute__((address_space(3))) void*)(st + NW * j * 1024), 16,
-                                               asrc[j], col, 0, 0);
+      copy16_to_lds(xt, (uint32_t)(nrows * Dm * 2), asrc[j], col, st + NW * j * 1024);
 #pragma unroll
     for (int j = half * CB / 2; j < (half + 1) * CB / 2; ++j)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(wr_, (__attribute__((address_space(3))) void*)(st + kAB + NW * j * 1024),
-                                               16, bsrc[j], col, 0, 0);
+      copy16_to_lds(wt, (uint32_t)(kNT * Dm * 2), bsrc[j], col, st + kAB + NW * j * 1024);
   };
   // the first stages are in flight while the positions are counted
 #pragma unroll
@@ -503,7 +496,6 @@ __global__ __launch_bounds__(kTh, (TsmTile<MT, NT, KT, R>::kWgPerCu)) void tsm_p
       *reinterpret_cast<u32x4v*>(out + ((size_t)b * p.S + row0 + row) * H * D + n0 + 8 * pc) = v;
     }
   }
-#endif
 }
 
 // w_out[n, c] = bf16(w[n, c] * gamma[c]): the RMS normalisation gain folded
