@@ -1124,15 +1124,18 @@ attn_fwd_f32_kernel(AttnParams p) {
           const int n = min(max(lim - (k0 + 4 * lg) + 1, 0), 4);
           vis[qb] = (1u << n) - 1u;
         }
+        // The maximum keeps a NaN (fmaxf would drop it, and with it the logit),
+        // so a row that sees one is NaN throughout. At -INFINITY the row has met
+        // only keys without weight, hidden or at that logit.
         float x[4], mx = -INFINITY;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           x[r] = (vis[qb] >> r) & 1u ? s[qb][r] * p.scale_log2 : -INFINITY;
-          mx = fmaxf(mx, x[r]);
+          mx = __builtin_elementwise_maximum(mx, x[r]);
         }
-        mx = max_xor32(max_xor16(mx));
-        const float m_new = fmaxf(m_run[qb], mx);
-        const bool none = m_new == -INFINITY;  // no visible key yet
+        mx = maximum_xor32(maximum_xor16(mx));
+        const float m_new = __builtin_elementwise_maximum(m_run[qb], mx);
+        const bool none = m_new == -INFINITY;
         const float alpha = none ? 1.f : __builtin_amdgcn_exp2f(m_run[qb] - m_new);
         l_run[qb] *= alpha;
 #pragma unroll
@@ -1207,19 +1210,20 @@ attn_fwd_f32_kernel(AttnParams p) {
       if (row < 16 && qi < len) {
         float m = msh[0][row];
 #pragma unroll
-        for (int x = 1; x < NW; ++x) m = fmaxf(m, msh[x][row]);
+        for (int x = 1; x < NW; ++x) m = __builtin_elementwise_maximum(m, msh[x][row]);
         f32x4 sum = {0.f, 0.f, 0.f, 0.f};
         float l = 0.f;
 #pragma unroll
         for (int x = 0; x < NW; ++x) {
-          if (msh[x][row] == -INFINITY && lsh[x][row] == 0.f) continue;  // a wave without a visible key
+          // 0 for a wave that met no key with a weight; NaN where no wave did (the
+          // row's visible logits are all -INFINITY: it has no softmax)
           const float f = __builtin_amdgcn_exp2f(msh[x][row] - m);
           l = fmaf(lsh[x][row], f, l);
           const f32x4 ox = *reinterpret_cast<const f32x4*>(&osh[x][row][d4]);
 #pragma unroll
           for (int e = 0; e < 4; ++e) sum[e] = fmaf(ox[e], f, sum[e]);
         }
-        const float inv = (l > 0.f) ? p.out_scale / l : 0.f;
+        const float inv = p.out_scale / l;  // every row sees a key: l >= 1 or NaN
         const size_t ob = ((size_t)(seq0 + qi) * p.Hq + h) * D + d4;
         sum *= inv;
         if (OUT == LITEVLM_F32) {

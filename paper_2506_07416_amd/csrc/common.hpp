@@ -53,6 +53,9 @@ __device__ __forceinline__ float2 pair_xor32(float x) {
 }
 __device__ __forceinline__ float max_xor16(float x) { const float2 p = pair_xor16(x); return fmaxf(p.x, p.y); }
 __device__ __forceinline__ float max_xor32(float x) { const float2 p = pair_xor32(x); return fmaxf(p.x, p.y); }
+// The maximum that keeps a NaN.
+__device__ __forceinline__ float maximum_xor16(float x) { const float2 p = pair_xor16(x); return __builtin_elementwise_maximum(p.x, p.y); }
+__device__ __forceinline__ float maximum_xor32(float x) { const float2 p = pair_xor32(x); return __builtin_elementwise_maximum(p.x, p.y); }
 __device__ __forceinline__ float sum_xor16(float x) { const float2 p = pair_xor16(x); return p.x + p.y; }
 __device__ __forceinline__ float sum_xor32(float x) { const float2 p = pair_xor32(x); return p.x + p.y; }
 

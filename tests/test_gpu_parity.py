@@ -744,3 +744,36 @@ def test_attention_f32_row_blocks(lens, D, dtype_out):
     for x in (o_inf, o2_inf):
         assert not torch.isfinite(x[sees]).any()
         check_attention(to_float64(x[~sees]), ref[~sees.cpu().numpy()], kind, "rows before the infinities")
+
+
+@pytest.mark.parametrize("D,causal", [(64, True), (128, True), (128, False)])
+@pytest.mark.parametrize("bound", [70, 8192])
+def test_attention_f32_nonfinite_logits(D, causal, bound):
+    """A NaN in a query or key row reaches exactly the rows whose visible logits
+    hold it, also where a whole 16-key tile of them (or all that a row sees) is
+    NaN; keys at logit -inf have no weight, and a row that sees nothing else has
+    no softmax (NaN). With one and with two row blocks to a workgroup."""
+    lens, Hq, Hkv = [70, 33, 16, 1], 4, 2
+    qb, kb, vb, _, cu = synth.random_attention_inputs(lens, Hq, Hkv, D, "f32", seed=91, peaked=True)
+    qb[..., 0] = 1.0  # so that a key with -inf there is at logit -inf for every query
+    cu_d = torch.from_numpy(cu).cuda()
+    scale = 1 / math.sqrt(D)
+
+    def keys(*local):
+        return [int(cu[i]) + j for i, n in enumerate(lens) for j in local if j < n]
+
+    # (what, tensor, rows, head dim, value)
+    for what, arr, rows, dim, val in [("NaN queries", 0, keys(0, 5, 40), 3, np.nan), ("NaN key 0", 1, keys(0), 3, np.nan),
+                                      ("NaN key 16", 1, keys(16), 3, np.nan), ("NaN keys 0-15", 1, keys(*range(16)), 3, np.nan),
+                                      ("NaN keys 32-47", 1, keys(*range(32, 48)), 3, np.nan),
+                                      ("-inf key 0", 1, keys(0), 0, -np.inf), ("-inf keys 0-15", 1, keys(*range(16)), 0, -np.inf),
+                                      ("-inf keys 16-31", 1, keys(*range(16, 32)), 0, -np.inf)]:
+        x = [qb.copy(), kb.copy(), vb.copy()]
+        x[arr][rows, :, dim] = val
+        o = lv.prefill_attn(*(to_device(y, "f32") for y in x), cu_d, bound, causal=causal)
+        torch.cuda.synchronize()
+        with np.errstate(invalid="ignore"):
+            ref = oracle.prefill_attention(*(y.astype(np.float64) for y in x), cu, Hq, Hkv, scale, causal=causal)
+        got, nan = to_float64(o), np.isnan(ref).any(axis=(1, 2))
+        assert np.array_equal(np.isnan(got), np.isnan(ref)), f"{what}: NaN in {np.isnan(got).sum()} elements, not {np.isnan(ref).sum()}"
+        check_attention(got[~nan], ref[~nan], "f32", what)
