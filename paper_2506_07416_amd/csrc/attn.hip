@@ -1136,11 +1136,12 @@ attn_fwd_f32_kernel(AttnParams p) {
         mx = maximum_xor32(maximum_xor16(mx));
         const float m_new = __builtin_elementwise_maximum(m_run[qb], mx);
         const bool none = m_new == -INFINITY;
-        const float alpha = none ? 1.f : __builtin_amdgcn_exp2f(m_run[qb] - m_new);
+        // exp2f: the bare instruction returns 0 below 2^-126
+        const float alpha = none ? 1.f : exp2f(m_run[qb] - m_new);
         l_run[qb] *= alpha;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          s[qb][r] = none ? 0.f : __builtin_amdgcn_exp2f(x[r] - m_new);
+          s[qb][r] = none ? 0.f : exp2f(x[r] - m_new);
           l_run[qb] += s[qb][r];
         }
         m_run[qb] = m_new;
@@ -1217,7 +1218,7 @@ attn_fwd_f32_kernel(AttnParams p) {
         for (int x = 0; x < NW; ++x) {
           // 0 for a wave that met no key with a weight; NaN where no wave did (the
           // row's visible logits are all -INFINITY: it has no softmax)
-          const float f = __builtin_amdgcn_exp2f(msh[x][row] - m);
+          const float f = exp2f(msh[x][row] - m);
           l = fmaf(lsh[x][row], f, l);
           const f32x4 ox = *reinterpret_cast<const f32x4*>(&osh[x][row][d4]);
 #pragma unroll

@@ -777,3 +777,24 @@ def test_attention_f32_nonfinite_logits(D, causal, bound):
         got, nan = to_float64(o), np.isnan(ref).any(axis=(1, 2))
         assert np.array_equal(np.isnan(got), np.isnan(ref)), f"{what}: NaN in {np.isnan(got).sum()} elements, not {np.isnan(ref).sum()}"
         check_attention(got[~nan], ref[~nan], "f32", what)
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("bound", [40, 8192])
+def test_attention_f32_small_probabilities(D, bound):
+    """Probabilities below the smallest normal number count: a key 135 powers of
+    two under the row's maximum, with values large enough to show, within a tile and
+    in another wave's."""
+    n, Hq, Hkv = 40, 2, 1
+    q, k, v = (np.zeros((n, h, D), np.float32) for h in (Hq, Hkv, Hkv))
+    q[..., 0] = 1.0
+    k[1:, :, 0] = -np.float32(135.0)
+    v[5] = 2.0 ** 100
+    v[37] = 2.0 ** 101
+    cu = np.array([0, n], np.int32)
+    o = lv.prefill_attn(*(torch.from_numpy(y).cuda() for y in (q, k, v)), torch.from_numpy(cu).cuda(), bound,
+                        softmax_scale=math.log(2.0))
+    torch.cuda.synchronize()
+    ref = oracle.prefill_attention(*(y.astype(np.float64) for y in (q, k, v)), cu, Hq, Hkv, math.log(2.0))
+    # 2^-135 keeps 14 bits as a subnormal, and the logit's rounding is 135 * 2^-23 of it
+    np.testing.assert_allclose(to_float64(o), ref, rtol=2.0 ** -13 + 135 * 2.0 ** -22)
