@@ -313,6 +313,7 @@ litevlm_status_t litevlm_prefill_attn(int32_t in_dtype, int32_t out_dtype, int32
       (D != 64 && D != 128) || max_seqlen < 0)
     return LITEVLM_ERR_BAD_SHAPE;
   if ((int64_t)B * max_seqlen > INT32_MAX / 2) return LITEVLM_ERR_BAD_SHAPE;
+  if (!prefill_attn_fits(in_dtype, B, Hq, max_seqlen)) return LITEVLM_ERR_BAD_SHAPE;
   if (causal != 0 && causal != 1) return LITEVLM_ERR_BAD_VALUE;
   if (!finite_pos(softmax_scale) || !finite_pos(q_scale) || !finite_pos(k_scale) ||
       !finite_pos(v_scale))

@@ -1052,6 +1052,8 @@ attn_fp8_kernel(AttnParams p) {
 // the four blocks e, so o[hd][e][x] is dim 64*hd + 16*(l/16) + 4*x + e of query
 // l % 16.
 constexpr int kF32Waves = 8;
+constexpr int kF32Rows = 32;    // rows of an item of a large grid
+constexpr int kF32Grid = 16384;  // a multiple of 8: item % 8 stays the XCD
 
 template <int D, bool CAUSAL, int OUT, int QB>
 __global__ void __launch_bounds__(64 * kF32Waves)
@@ -1240,6 +1242,8 @@ attn_fwd_f32_kernel(AttnParams p) {
 }
 static_assert(16 * (128 / 4) <= 64 * kF32Waves, "one 16-byte piece of a row block per thread");
 
+constexpr int kRows = 128;  // rows of an item of the bf16 and E4M3 grids
+
 template <int D, bool CAUSAL, int OUT>
 static void launch_typed(const AttnArgs& a, AttnParams& p, hipStream_t stream) {
   // bf16 grids of at most two 128-row workgroups per CU (256 CUs) take the
@@ -1261,16 +1265,21 @@ static void launch_typed(const AttnArgs& a, AttnParams& p, hipStream_t stream) {
     // reads per product). Keys go to the waves alike in both, so a row's result
     // does not depend on the bound.
     const bool one = (long long)((a.max_seqlen + 15) / 16) * a.Hq * a.B <= 2LL * 256;
-    const int bm32 = one ? 16 : 32;
+    const int bm32 = one ? 16 : kF32Rows;
     p.n_mtiles = (a.max_seqlen + bm32 - 1) / bm32;
     p.n_work = p.n_mtiles * a.Hq * a.B;
     p.per_xcd = (p.n_work + 7) / 8;
-    const dim3 g32((unsigned)std::min(8 * p.per_xcd, 1 << 22));  // a multiple of 8: L % 8 stays the XCD
+    // At most kF32Grid workgroups, each striding over the items: a bound far above
+    // the lengths makes items that end at once, cheaper in a loop than as
+    // workgroups of eight waves (64 tokens, 32 heads, bound 65536: 124 us, a
+    // workgroup each 225); with half as many, 3 samples of up to 3000
+    // tokens and 32 heads take 1011 us where this takes 998.
+    const dim3 g32((unsigned)std::min(8 * p.per_xcd, kF32Grid));
     if (one) hipLaunchKernelGGL((attn_fwd_f32_kernel<D, CAUSAL, OUT, 1>), g32, dim3(64 * kF32Waves), 0, stream, p);
     else hipLaunchKernelGGL((attn_fwd_f32_kernel<D, CAUSAL, OUT, 2>), g32, dim3(64 * kF32Waves), 0, stream, p);
     return;
   }
-  const int bm = 128;
+  const int bm = kRows;
   p.n_mtiles = (a.max_seqlen + bm - 1) / bm;
   p.n_work = p.n_mtiles * a.Hq * a.B;
   p.per_xcd = (p.n_work + 7) / 8;
@@ -1290,6 +1299,13 @@ static void launch_d(const AttnArgs& a, AttnParams& p, hipStream_t stream) {
     if (a.out_dtype == LITEVLM_BF16) launch_typed<D, false, LITEVLM_BF16>(a, p, stream);
     else launch_typed<D, false, LITEVLM_F32>(a, p, stream);
   }
+}
+
+bool prefill_attn_fits(int in_dtype, int B, int Hq, int max_seqlen) {
+  // (the smaller tiles of the small grids are only taken below 512 workgroups)
+  const int bm = in_dtype == LITEVLM_F32 ? kF32Rows : kRows;
+  // (a strided loop over the items steps at most kF32Grid past the last)
+  return ((int64_t)max_seqlen + bm - 1) / bm * Hq * B <= INT32_MAX - 2 * kF32Grid;
 }
 
 hipError_t launch_prefill_attn(const AttnArgs& a, hipStream_t stream) {

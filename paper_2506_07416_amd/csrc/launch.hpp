@@ -73,6 +73,9 @@ struct AttnArgs {
   float out_scale;         // v_scale
   void* o;
 };
+// Whether the work items of the launch (row tiles of the bound x heads x samples)
+// can be counted in an int.
+bool prefill_attn_fits(int in_dtype, int B, int Hq, int max_seqlen);
 hipError_t launch_prefill_attn(const AttnArgs& a, hipStream_t stream);
 
 // Workspace of the decode step: per (sample, query head, key split) the

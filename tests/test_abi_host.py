@@ -205,6 +205,16 @@ def test_prefill_attn_validation():
     assert pa(cu=A + 1) == _abi.ERR_MISALIGNED
 
 
+@pytest.mark.parametrize("dtype,rows", [(_abi.F32, 32), (_abi.BF16, 128), (_abi.FP8_E4M3, 128)])
+def test_prefill_attn_refuses_uncountable_work(dtype, rows):
+    """Row tiles x heads x samples past the range of an int: refused on the host,
+    also where the product would wrap to a small positive number."""
+    ml = 2 ** 30 - 1
+    tiles = 2 ** 30 // rows
+    for Hq in (2 ** 31 // tiles, 2 ** 32 // tiles + 1):
+        assert pa(ind=dtype, B=1, Hq=Hq, Hkv=1, ml=ml) == _abi.ERR_BAD_SHAPE
+
+
 def test_binding_fails_loudly_without_library(monkeypatch, tmp_path):
     monkeypatch.setattr(_abi, "_LIB", None)
     monkeypatch.setattr(_abi, "LIB_PATH", str(tmp_path / "missing.so"))

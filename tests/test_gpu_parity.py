@@ -715,8 +715,8 @@ def test_attention_grid_bound_above_lengths(dtype):
 def test_attention_f32_row_blocks(lens, D, dtype_out):
     """The fp32 kernel at the edges of its 16-row blocks and 16-key tiles, with one
     and with two blocks to a workgroup (the second by a bound that makes the grid
-    large), bitwise alike; a value row of infinities reaches exactly the rows that
-    see it."""
+    large, the third by one that makes workgroups take several items), bitwise
+    alike; a value row of infinities reaches exactly the rows that see it."""
     Hq, Hkv = 4, 2
     qb, kb, vb, _, cu = synth.random_attention_inputs(lens, Hq, Hkv, D, "f32", seed=77, peaked=True)
     q, k, v = (to_device(x, "f32") for x in (qb, kb, vb))
@@ -726,13 +726,14 @@ def test_attention_f32_row_blocks(lens, D, dtype_out):
     v_inf = v.clone()
     v_inf[bad] = math.inf
     got = []
-    for bound in (max(lens), 8192):
+    for bound in (max(lens), 8192, 1 << 18):
         o = lv.prefill_attn(q, k, v, cu_d, bound, out_dtype=odt)
         o_inf = lv.prefill_attn(q, k, v_inf, cu_d, bound, out_dtype=odt)
         got.append((o, o_inf))
     torch.cuda.synchronize()
-    (o, o_inf), (o2, o2_inf) = got
-    assert torch.equal(o.view(torch.uint8), o2.view(torch.uint8))
+    o, o_inf = got[0]
+    for other, _ in got[1:]:
+        assert torch.equal(o.view(torch.uint8), other.view(torch.uint8))
     q64, k64, v64 = (oracle.litevlm.decode_stored(x, "f32", 1.0) for x in (qb, kb, vb))
     ref = oracle.prefill_attention(q64, k64, v64, cu, Hq, Hkv, 1 / math.sqrt(D))
     kind = attn_kind("f32" if dtype_out == "f32" else "bf16")
@@ -741,7 +742,7 @@ def test_attention_f32_row_blocks(lens, D, dtype_out):
     for i, n in enumerate(lens):
         if n > 1:
             sees[int(cu[i]) + (3 * n) // 4:int(cu[i + 1])] = True
-    for x in (o_inf, o2_inf):
+    for _, x in got:
         assert not torch.isfinite(x[sees]).any()
         check_attention(to_float64(x[~sees]), ref[~sees.cpu().numpy()], kind, "rows before the infinities")
 
