@@ -496,8 +496,9 @@ __global__ __launch_bounds__(psm_head_threads(D)) void psm_head_kernel(const flo
       }
       a = row16_sum(a) * rstd * scale;
       c = row16_sum(c) * rstd;
-      const float mn = fmaxf(m[v], a);
-      const float al = __builtin_amdgcn_exp2f(m[v] - mn), e = __builtin_amdgcn_exp2f(a - mn);  // first row: al = exp2(-inf) = 0
+      // a row at -inf has no weight, before the first finite one too
+      const float mn = fmaxf(m[v], a), ms = mn == -INFINITY ? 0.f : mn;
+      const float al = __builtin_amdgcn_exp2f(m[v] - ms), e = __builtin_amdgcn_exp2f(a - ms);  // first row: al = exp2(-inf) = 0
       l[v] = fmaf(l[v], al, e);
       z[v] = fmaf(z[v], al, e * c);
       m[v] = mn;

@@ -79,3 +79,38 @@ def test_psm_edges(name, c):
     # the bound of the shapes above: bf16 GEMM inputs over at most two layers
     assert np.all(err <= PSM_ATOL + PSM_RTOL * np.abs(ref)), f"{name}: max err {err.max():.3g}"
     log(f"{name}: logits max abs err {err.max():.2e} (|ref| max {np.abs(ref).max():.2f})")
+
+
+def param(par, c, name):
+    """The named part of the flat parameter vector (a view)."""
+    off = 0
+    for nm, shape in OP.param_layout(c["d"], c["dff"], c["N"], c["L"]):
+        n = int(np.prod(shape))
+        if nm == name:
+            return par[off:off + n].reshape(shape)
+        off += n
+    raise KeyError(name)
+
+
+@pytest.mark.parametrize("d", [256, 512])
+def test_psm_cross_logits_at_minus_infinity(d):
+    """Tokens whose cross-attention logit leaves the range of fp32 downwards have
+    no weight, wherever they stand among the others."""
+    c = dict(B=1, T=40, d=d, H=4, dff=64, N=3, L=1)
+    emb, par = synth.psm_inputs(c["B"], c["T"], d, c["dff"], c["N"], c["L"], seed=5400)
+    for n in ("l0.w_o", "l0.b_o", "l0.w_down", "l0.b_down", "latents", "b_ck", "lnf_b"):
+        param(par, c, n)[:] = 0.0  # the encoder passes the embeddings on
+    # the final norm leaves rows of +-1 as they are; logits of -1e38 * d or (rows orthogonal to p) 0
+    i = np.arange(d)
+    p, r = np.where(i % 2 == 0, 1.0, -1.0), np.where(i % 4 < 2, 1.0, -1.0)
+    param(par, c, "lnf_g")[:] = 1.0
+    param(par, c, "b_cq")[:] = 1e30 * p
+    param(par, c, "w_ck")[:] = 1e8 * np.eye(d)
+    emb[0] = r
+    emb[0, 3:30:4] = -r
+    emb[0, [0, 7, 33]] = -p
+    out = lv.psm_forward(torch.from_numpy(emb).cuda(), torch.from_numpy(par).cuda(), c["H"], c["dff"], c["N"], c["L"])
+    torch.cuda.synchronize()
+    ref = OP.psm_forward(emb.astype(np.float64), par.astype(np.float64), c["H"], c["dff"], c["N"], c["L"])
+    err = np.abs(out.cpu().numpy().astype(np.float64) - ref)
+    assert np.all(err <= PSM_ATOL + PSM_RTOL * np.abs(ref)), f"got {out.tolist()}, reference {ref.tolist()}"
