@@ -63,7 +63,7 @@ enum { kOutBf16 = 0, kOutGelu = 1, kOutResid = 2 };
 // b_head_v, stage 2 (a later launch) u_v = W_ck^T q_v. All fp32.
 struct PsmFold {
   int stage, d, n_views;  // stage 0: nothing
-  const float *lat, *w_cq, *b_cq, *w_ck, *w_cv, *b_cv, *w_hd, *b_hd;
+  const float *lat, *w_cq, *b_cq, *w_ck, *b_ck, *w_cv, *b_cv, *w_hd, *b_hd;
   float *qv, *u, *g, *cst;  // [N, d], [N, d], [N, d], [N]
 };
 
@@ -155,7 +155,12 @@ __device__ void psm_fold(const PsmFold& f, int blk, float* lds) {
   if (v < f.n_views) {
     float s = 0.f;
 #pragma unroll
-    for (int i = 0; i < D / 64; ++i) s = fmaf(f.w_hd[(size_t)v * D + lane + 64 * i], f.b_cv[lane + 64 * i], s);
+    for (int i = 0; i < D / 64; ++i) {
+      s = fmaf(f.w_hd[(size_t)v * D + lane + 64 * i], f.b_cv[lane + 64 * i], s);
+      // b_ck adds a constant to every token's logit, which the softmax cancels
+      // unless it is no number or infinite
+      s = fmaf(0.f, f.b_ck[lane + 64 * i], s);
+    }
     s = psm_wave_sum(s);
     if (lane == 0) f.cst[v] = s + f.b_hd[v];
   }
@@ -580,7 +585,8 @@ hipError_t run(const PsmArgs& a, hipStream_t s) {
   fold.w_cq = fold.lat + (size_t)a.n_views * d;
   fold.b_cq = fold.w_cq + (size_t)d * d;
   fold.w_ck = fold.b_cq + d;
-  fold.w_cv = fold.w_ck + (size_t)d * d + d;  // b_ck adds a constant to every token's logit: no effect
+  fold.b_ck = fold.w_ck + (size_t)d * d;
+  fold.w_cv = fold.b_ck + d;
   fold.b_cv = fold.w_cv + (size_t)d * d;
   fold.w_hd = fold.b_cv + d;
   fold.b_hd = fold.w_hd + (size_t)a.n_views * d;

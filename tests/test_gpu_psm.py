@@ -114,3 +114,21 @@ def test_psm_cross_logits_at_minus_infinity(d):
     ref = OP.psm_forward(emb.astype(np.float64), par.astype(np.float64), c["H"], c["dff"], c["N"], c["L"])
     err = np.abs(out.cpu().numpy().astype(np.float64) - ref)
     assert np.all(err <= PSM_ATOL + PSM_RTOL * np.abs(ref)), f"got {out.tolist()}, reference {ref.tolist()}"
+
+
+@pytest.mark.parametrize("d", [256, 512])
+@pytest.mark.parametrize("value", [np.nan, np.inf])
+def test_psm_parameters_that_are_no_numbers_show(d, value):
+    """A NaN or an infinity in any parameter leaves no finite logit where the
+    oracle's is not (b_ck, whose finite values the softmax cancels, included)."""
+    c = dict(B=2, T=20, d=d, H=4, dff=64, N=3, L=2)
+    emb, par = synth.psm_inputs(c["B"], c["T"], d, c["dff"], c["N"], c["L"], seed=5500)
+    for name, _ in OP.param_layout(d, c["dff"], c["N"], c["L"]):
+        x = par.copy()
+        a = param(x, c, name).reshape(-1)
+        a[a.size // 2] = value
+        out = lv.psm_forward(torch.from_numpy(emb).cuda(), torch.from_numpy(x).cuda(), c["H"], c["dff"], c["N"], c["L"])
+        torch.cuda.synchronize()
+        with np.errstate(all="ignore"):
+            ref = OP.psm_forward(emb.astype(np.float64), x.astype(np.float64), c["H"], c["dff"], c["N"], c["L"])
+        assert np.array_equal(np.isfinite(out.cpu().numpy()), np.isfinite(ref)), f"{name}: {out.tolist()}, reference {ref.tolist()}"
