@@ -446,9 +446,6 @@ __global__ __launch_bounds__(kTh, (TsmTile<MT, NT, KT, R>::kWgPerCu)) void tsm_p
     const int col = 32 * cbl[c] + l32;  // tile feature of the first-half element; its partner is D/2 on
     const int d = (32 * cbl[c]) % D + l32;  // element of the first half of its head (d < D/2)
     const double turns_per_pos = exp2(-(2.0 * d / D) * p.log2_theta) * 0.15915494309189535;  // / (2 pi)
-    float s1[3], c1[3];  // of 1, 2 and 3 positions
-#pragma unroll
-    for (int k = 0; k < 3; ++k) sincos_turns((k + 1) * turns_per_pos, s1[k], c1[k]);
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
@@ -457,19 +454,8 @@ __global__ __launch_bounds__(kTh, (TsmTile<MT, NT, KT, R>::kWgPerCu)) void tsm_p
         const f32x4 f = *reinterpret_cast<const f32x4*>(rs + row4);
         const i32x4 ps = *reinterpret_cast<const i32x4*>(pos + row4);
         float sn[4], cs[4];
-        sincos_turns((double)ps[0] * turns_per_pos, sn[0], cs[0]);
-        // four rows in sequence (all but where tokens are dropped between them):
-        // the angle sums instead of a sine, a cosine and a double reduction each
-        if (__all(ps[1] == ps[0] + 1 && ps[2] == ps[0] + 2 && ps[3] == ps[0] + 3)) {
 #pragma unroll
-          for (int e = 1; e < 4; ++e) {
-            sn[e] = fmaf(sn[0], c1[e - 1], cs[0] * s1[e - 1]);
-            cs[e] = fmaf(cs[0], c1[e - 1], -(sn[0] * s1[e - 1]));
-          }
-        } else {
-#pragma unroll
-          for (int e = 1; e < 4; ++e) sincos_turns((double)ps[e] * turns_per_pos, sn[e], cs[e]);
-        }
+        for (int e = 0; e < 4; ++e) sincos_turns((double)ps[e] * turns_per_pos, sn[e], cs[e]);
         float y1[4], y2[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {

@@ -154,3 +154,21 @@ def test_tsm_scoring_chain_and_hidden_gather(cfg, B):
     log(f"cfg{cfg} B={case.B}: score rel err from bf16 q/k median {np.median(rel):.2e} max {rel.max():.2e}; "
         f"lengths {np.diff(cu).tolist()}")
     assert np.median(rel) < 1e-2 and rel.max() < 1e-1
+
+
+@pytest.mark.parametrize("Hq,Hkv,D", [(8, 4, 128), (8, 4, 64), (4, 1, 128)])
+def test_tsm_rotation_depends_on_the_position_only(Hq, Hkv, D):
+    """A key row at a position is the same bits whether the row before it in
+    memory is its predecessor in the sequence or a dropped token: every row's angle
+    is reduced for itself, none is derived from its neighbour's."""
+    n, Dm, T = 1024, 512, 16
+    hid, _, wq, wk = synth.tsm_inputs(1, n + T, Dm, Hq, Hkv, D, seed=4500)
+    x, wq, wk = (to_device(y, "bf16") for y in (hid, wq, wk))
+    _, k = lv.tsm_qk(x, torch.ones((1, n + T), dtype=torch.uint8, device="cuda"), n, wq, wk, Hq, Hkv, D)
+    x2 = torch.cat([x[:, :n].repeat_interleave(2, dim=1), x[:, n:]], dim=1).contiguous()
+    keep = torch.ones((1, 2 * n + T), dtype=torch.uint8, device="cuda")
+    keep[0, 1:2 * n:2] = 0
+    _, k2 = lv.tsm_qk(x2, keep, 2 * n, wq, wk, Hq, Hkv, D)
+    torch.cuda.synchronize()
+    differ = (k[0, :n].view(torch.int16) != k2[0, 0:2 * n:2].view(torch.int16)).sum()
+    assert differ == 0, f"{int(differ)} elements differ"
