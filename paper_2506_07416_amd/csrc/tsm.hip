@@ -70,7 +70,7 @@ struct TsmParams {
   uint16_t* k;          // bf16 [B, S, Hkv, D]
   int B, S, V_full, Dm, Hq, Hkv;
   int mk, nk, mq, nq, gk, gq;           // gk, gq: key and query row tiles (B*mk, B*mq)
-  int compact;                          // leave out the key row tiles without a kept row
+  int turn;                             // key row tiles dealt in turn to each XCD
   float eps;
   double log2_theta;
 };
@@ -109,67 +109,31 @@ __global__ __launch_bounds__(kTh, (TsmTile<MT, NT, KT, R>::kWgPerCu)) void tsm_p
   constexpr int CBW = Tl::kCBW;  // 32-column blocks per wave
   __shared__ __attribute__((aligned(1024))) uint8_t lds[Tl::kLdsB];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  // ---- work item. The items are the key row tiles with each of their feature
-  // tiles, then the query row tiles with theirs; an XCD takes a contiguous range
-  // (a row tile's feature tiles share its rows of x in that L2), the ranges
-  // equal to within one item.
-  bool isq;
+  // ---- work item: a key row tile with one of its feature tiles, or a query row
+  // tile with one of its. The first 8*turn key row tiles go to the XCDs in turn,
+  // each with all its feature tiles (they share its rows of x in that L2); the other
+  // items follow in contiguous ranges, equal to within one item.
+  bool isq = false;
   int b, mt, nt;
   {
-    int nwork = p.gk;  // key row tiles to compute
-    if (p.compact) {
-      // Only those that hold a kept row: every workgroup finds them from the
-      // keep bytes, 16 at a time (host check: S and the mask are multiples of 16),
-      // all in flight together. The flags go into the ring, unused until the
-      // stage copies start.
-      for (int g = tid; g < p.gk; g += kTh) lds[g] = 0;
-      __syncthreads();
-      const uint4* k16 = reinterpret_cast<const uint4*>(p.keep);
-      const int n16 = p.B * (p.S / 16), s16 = p.S / 16;
-      constexpr int U = 16;
-      for (int p0 = 0; p0 < n16; p0 += U * kTh) {
-        uint4 u[U];
-#pragma unroll
-        for (int i = 0; i < U; ++i) u[i] = k16[min(p0 + i * kTh + tid, n16 - 1)];
-#pragma unroll
-        for (int i = 0; i < U; ++i) {
-          const int pc = min(p0 + i * kTh + tid, n16 - 1), pb = pc / s16;
-          if ((u[i].x | u[i].y | u[i].z | u[i].w) != 0u) lds[pb * p.mk + (pc - pb * s16) / (kMT / 16)] = 1;
-        }
-      }
-      __syncthreads();
-      nwork = 0;
-      for (int c0 = 0; c0 < p.gk; c0 += 64) nwork += __popcll(__ballot(c0 + lane < p.gk && lds[c0 + lane] != 0));
+    const int x = blockIdx.x & 7, j = blockIdx.x >> 3, nturn = p.turn * p.nk;
+    int grp;
+    if (j < nturn) {
+      grp = x + 8 * (j / p.nk);
+      nt = j % p.nk;
+    } else {
+      const int nkey = (p.gk - 8 * p.turn) * p.nk, total = nkey + p.gq * p.nq;
+      const int i0 = (int)(((int64_t)x * total) >> 3), i1 = (int)(((int64_t)(x + 1) * total) >> 3);
+      int item = i0 + j - nturn;
+      if (item >= i1) return;
+      isq = item >= nkey;
+      if (isq) item -= nkey;
+      const int per = isq ? p.nq : p.nk;
+      grp = item / per;
+      nt = item - grp * per;
+      if (!isq) grp += 8 * p.turn;
     }
-    const int total = nwork * p.nk + p.gq * p.nq;
-    const int x = blockIdx.x & 7;
-    const int i0 = (int)(((int64_t)x * total) >> 3), i1 = (int)(((int64_t)(x + 1) * total) >> 3);
-    int item = i0 + (int)(blockIdx.x >> 3);
-    if (item >= i1) return;
-    isq = item >= nwork * p.nk;
-    if (isq) item -= nwork * p.nk;
-    const int per = isq ? p.nq : p.nk, mm = isq ? p.mq : p.mk;
-    int grp = item / per;
-    nt = item - grp * per;
-    if (p.compact) {
-      if (!isq) {
-        // the working tile of rank grp (every wave finds the same)
-        const int rk = grp;
-        int seen = 0;
-        for (int c0 = 0; c0 < p.gk; c0 += 64) {
-          const bool f = c0 + lane < p.gk && lds[c0 + lane] != 0;
-          const uint64_t m = __ballot(f);
-          const int cnt = __popcll(m);
-          if (rk >= seen && rk < seen + cnt) {
-            const int before = __popcll(m & ((1ull << lane) - 1ull));
-            const uint64_t sel = __ballot(f && before == rk - seen);
-            grp = c0 + __ffsll((unsigned long long)sel) - 1;
-          }
-          seen += cnt;
-        }
-      }
-      __syncthreads();  // every wave has read the flags: the ring may be filled
-    }
+    const int mm = isq ? p.mq : p.mk;
     b = grp / mm;
     mt = grp - b * mm;
   }
@@ -513,6 +477,15 @@ hipError_t launch_tsm_qk(const TsmArgs& a, hipStream_t stream) {
   p.eps = a.eps;
   p.log2_theta = log2((double)a.rope_theta);
   const int T = a.S - a.V_full;
+  // A dropped view is a run of row tiles whose workgroups end at once. Dealt in
+  // turn the runs spread over the XCDs, where contiguous ranges leave the XCDs
+  // that hold them idle (eight prompts of 6 x 1024 visual and 120 text tokens, 0-4
+  // views dropped: 410 -> 347 us; one, 3 dropped: 60 -> 51 us). Finding the working
+  // tiles from the mask in every workgroup deals them exactly, but costs each 2.3
+  // us before its first copy: 356 us for the eight, 54 for the one. It pays only
+  // where a tile more or less decides about a round of the chip (five prompts, 32/8
+  // heads of 64, width 1024, 3 of 30 views dropped: 56 against 65 us). Below four
+  // tiles an XCD the ranges are as good (318 tokens, batch 4: 24.6 against 26.1 us).
   auto setup = [&](int MT, int NT) {
     p.mk = (a.S + MT - 1) / MT;
     p.nk = a.Hkv * a.D / NT;
@@ -520,24 +493,22 @@ hipError_t launch_tsm_qk(const TsmArgs& a, hipStream_t stream) {
     p.nq = a.Hq * a.D / NT;
     p.gk = a.B * p.mk;
     p.gq = a.B * p.mq;
-    p.compact = 0;
-    return dim3((unsigned)(8 * (((int64_t)p.gk * p.nk + (int64_t)p.gq * p.nq + 7) / 8)));
+    p.turn = a.token_keep && p.gk >= 32 ? p.gk / 8 : 0;
+    const int64_t rest = (int64_t)(p.gk - 8 * p.turn) * p.nk + (int64_t)p.gq * p.nq;
+    return dim3((unsigned)(8 * ((int64_t)p.turn * p.nk + (rest + 7) / 8)));
   };
   // Workgroups of a tile shape with every view kept (the host does not know the mask).
   auto items = [&](int MT, int NT) {
     return (int64_t)a.B * (((a.S + MT - 1) / MT) * (int64_t)(a.Hkv * a.D / NT) + ((T + MT - 1) / MT) * (int64_t)(a.Hq * a.D / NT));
   };
   const bool wide = (a.Hkv * a.D) % 256 == 0 && (a.Hq * a.D) % 256 == 0;
-  auto launch = [&](auto kern, int MT, int NT, int ring) {
+  auto launch = [&](auto kern, int MT, int NT) {
     const dim3 grid = setup(MT, NT);
-    // the dealing workgroups read the mask in 16-byte pieces and keep one flag
-    // byte per key row tile in the stage ring
-    p.compact = a.token_keep && a.S % 16 == 0 && (reinterpret_cast<uintptr_t>(a.token_keep) & 15) == 0 && p.gk <= ring;
     hipLaunchKernelGGL(kern, grid, dim3(kTh), 0, stream, p);
   };
-#define LITEVLM_TSM(MT, NT, KT, R)                                                                  \
-  (a.D == 128 ? launch(tsm_proj_kernel<128, MT, NT, KT, R>, MT, NT, TsmTile<MT, NT, KT, R>::kRingB) \
-              : launch(tsm_proj_kernel<64, MT, NT, KT, R>, MT, NT, TsmTile<MT, NT, KT, R>::kRingB))
+#define LITEVLM_TSM(MT, NT, KT, R)                                           \
+  (a.D == 128 ? launch(tsm_proj_kernel<128, MT, NT, KT, R>, MT, NT) \
+              : launch(tsm_proj_kernel<64, MT, NT, KT, R>, MT, NT))
   // One 128 x 128 tile per CU or fewer: the smallest tile's K loop is the
   // shortest chain, in 32-column stages four deep (1536 visual tokens, 32/8 heads,
   // width 4096: 41 us against 54 in 128 x 256 tiles; 392 tokens, 16/8 heads,

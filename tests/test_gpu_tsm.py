@@ -69,17 +69,23 @@ def check(got, ref, what):
     ("ragged rows, D=64, GQA 8/2", dict(B=1, N=2, Tv=100, T=37, Hq=8, Hkv=2, D=64, n_masked=0), 192),
     ("MHA 16/16 D=128, 2 of 6 views dropped", dict(B=1, N=6, Tv=40, T=64, Hq=16, Hkv=16, D=128,
                                                    n_masked=2), 512),
-    # LITEVLM_MAX_BATCH samples: 256 key row tiles of 256, the tiles dealt by rank
+    # LITEVLM_MAX_BATCH samples, a key row tile each, dealt to the XCDs in turn (128 x 256 tiles)
     ("256 samples of 2 views x 48 + 16 text, GQA 4/2", dict(B=256, N=2, Tv=48, T=16, Hq=4, Hkv=2, D=128,
                                                            n_masked=(0, 1)), 256),
-    # the other tile shapes: 256 x 256 (the mask read 16 bytes at a time, or by row ranges where
-    # a row of it is no multiple of 16), 128 x 256, and 256 x 128 where no 256 features divide
+    # the other tile shapes: 256 x 256, 128 x 256, and 256 x 128 where no 256 features divide
     ("256 x 256 tiles, D=128", dict(B=72, N=2, Tv=104, T=32, Hq=4, Hkv=2, D=128, n_masked=(0, 1)), 128),
     ("256 x 256 tiles, D=64, odd rows", dict(B=72, N=2, Tv=100, T=33, Hq=8, Hkv=4, D=64, n_masked=(0, 1)), 64),
     ("128 x 256 tiles, D=128, odd rows", dict(B=36, N=2, Tv=100, T=33, Hq=4, Hkv=2, D=128, n_masked=(0, 1)), 192),
     ("128 x 256 tiles, D=64", dict(B=36, N=2, Tv=104, T=32, Hq=8, Hkv=4, D=64, n_masked=(0, 1)), 64),
     ("256 x 128 tiles, D=128", dict(B=72, N=3, Tv=69, T=33, Hq=4, Hkv=1, D=128, n_masked=(0, 2)), 320),
     ("256 x 128 tiles, D=64, odd rows", dict(B=72, N=2, Tv=101, T=33, Hq=8, Hkv=2, D=64, n_masked=(0, 1)), 64),
+    # several row tiles a sample, some of them (views of 301 or 601 rows) dropped whole, with kept
+    # rows before them, in each tile shape; key row tiles left over when the XCDs have had theirs in turn
+    ("128 x 128 tiles, whole tiles dropped", dict(B=5, N=3, Tv=301, T=33, Hq=4, Hkv=2, D=128, n_masked=(0, 2)), 64),
+    ("128 x 256 tiles, whole tiles dropped", dict(B=17, N=3, Tv=301, T=33, Hq=4, Hkv=2, D=128, n_masked=(0, 2)), 64),
+    ("256 x 256 tiles, whole tiles dropped", dict(B=21, N=2, Tv=601, T=16, Hq=4, Hkv=2, D=128, n_masked=(0, 1)), 64),
+    ("256 x 128 tiles, whole tiles dropped", dict(B=24, N=3, Tv=512, T=16, Hq=4, Hkv=1, D=128, n_masked=(0, 2)), 64),
+    ("256 x 128 tiles, D=64, whole tiles dropped", dict(B=23, N=3, Tv=515, T=21, Hq=8, Hkv=2, D=64, n_masked=(0, 2)), 64),
 ])
 def test_tsm_matches_oracle(name, over, Dm):
     case = synth.config_case(2, **over)
@@ -100,8 +106,8 @@ def test_tsm_without_token_keep_uses_plain_positions():
 def test_tsm_full_size(cfg, B):
     """The 6x1024 + 128 shape with model width Hq*D = 4096 (batch 1, and the
     ragged batch with 0-4 views dropped per sample, cut to 2 and 3 samples to
-    keep the float64 oracle within seconds; 3 samples take the 256 x 256 tiles):
-    every key row and text query row."""
+    keep the float64 oracle within seconds; 2 samples take the 256 x 256 tiles, 1
+    and 3 the 128 x 256 ones): every key row and text query row."""
     case = synth.config_case(cfg) if B == 1 else synth.config_case(cfg, B=B)
     q, k, qr, kr = run(case, case.Hq * case.D, seed=4300 + cfg)
     sq = check(q, qr, f"cfg{cfg} q")
@@ -172,3 +178,23 @@ def test_tsm_rotation_depends_on_the_position_only(Hq, Hkv, D):
     torch.cuda.synchronize()
     differ = (k[0, :n].view(torch.int16) != k2[0, 0:2 * n:2].view(torch.int16)).sum()
     assert differ == 0, f"{int(differ)} elements differ"
+
+
+@pytest.mark.parametrize("shift", [1, 8])
+def test_tsm_mask_at_any_address(shift):
+    """token_keep is a byte array: the result does not depend on its alignment."""
+    case = synth.config_case(2, B=5, N=3, Tv=301, T=33, Hq=4, Hkv=2, D=128, n_masked=(0, 2))
+    Dm = 64
+    hid, _, wq, wk = synth.tsm_inputs(case.B, case.S, Dm, case.Hq, case.Hkv, case.D, seed=4600)
+    x, wq, wk = (to_device(y, "bf16") for y in (hid, wq, wk))
+    _, tk, _ = lv.patch_select(torch.from_numpy(case.view_logit).cuda(), case.view_offsets, case.S, case.w_lexical,
+                               case.threshold)
+    moved = torch.empty(tk.numel() + 16, dtype=torch.uint8, device="cuda")[shift:shift + tk.numel()].view(tk.shape)
+    moved.copy_(tk)
+    out = []
+    for keep in (tk, moved):
+        q0, k0 = (torch.zeros((case.B, case.S, h, case.D), dtype=torch.bfloat16, device="cuda") for h in (case.Hq, case.Hkv))
+        out.append(lv.tsm_qk(x, keep, case.V_full, wq, wk, case.Hq, case.Hkv, case.D, q=q0, k=k0))
+    torch.cuda.synchronize()
+    for a, b in zip(*out):
+        assert torch.equal(a.view(torch.int16), b.view(torch.int16))
