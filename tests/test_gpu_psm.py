@@ -69,6 +69,8 @@ EDGES = [
     ("64 x 64 tiles, d 512, 1450 rows", dict(B=2, T=725, d=512, H=4, dff=1088, N=3, L=1)),
     ("64 x 128 tiles, d 512, 2060 rows", dict(B=4, T=515, d=512, H=8, dff=2048, N=6, L=1)),
     ("64 x 128 tiles, d 256, 5500 rows", dict(B=20, T=275, d=256, H=4, dff=1024, N=6, L=1)),
+    # the residual GEMMs (bf16 rows in) reach 64 x 128 from 8129 rows at d 512
+    ("64 x 128 tiles in the residual GEMMs too, 8150 rows", dict(B=50, T=163, d=512, H=8, dff=576, N=6, L=1)),
 ]
 
 

@@ -79,11 +79,11 @@ def check(got, ref, what):
     ("128 x 256 tiles, D=64", dict(B=36, N=2, Tv=104, T=32, Hq=8, Hkv=4, D=64, n_masked=(0, 1)), 64),
     ("256 x 128 tiles, D=128", dict(B=72, N=3, Tv=69, T=33, Hq=4, Hkv=1, D=128, n_masked=(0, 2)), 320),
     ("256 x 128 tiles, D=64, odd rows", dict(B=72, N=2, Tv=101, T=33, Hq=8, Hkv=2, D=64, n_masked=(0, 1)), 64),
-    # several row tiles a sample, some of them (views of 301 or 601 rows) dropped whole, with kept
+    # several row tiles a sample, some of them (views of 301 or 512 rows) dropped whole, with kept
     # rows before them, in each tile shape; key row tiles left over when the XCDs have had theirs in turn
     ("128 x 128 tiles, whole tiles dropped", dict(B=5, N=3, Tv=301, T=33, Hq=4, Hkv=2, D=128, n_masked=(0, 2)), 64),
     ("128 x 256 tiles, whole tiles dropped", dict(B=17, N=3, Tv=301, T=33, Hq=4, Hkv=2, D=128, n_masked=(0, 2)), 64),
-    ("256 x 256 tiles, whole tiles dropped", dict(B=21, N=2, Tv=601, T=16, Hq=4, Hkv=2, D=128, n_masked=(0, 1)), 64),
+    ("256 x 256 tiles, whole tiles dropped", dict(B=32, N=3, Tv=301, T=33, Hq=4, Hkv=2, D=128, n_masked=(0, 2)), 64),
     ("256 x 128 tiles, whole tiles dropped", dict(B=24, N=3, Tv=512, T=16, Hq=4, Hkv=1, D=128, n_masked=(0, 2)), 64),
     ("256 x 128 tiles, D=64, whole tiles dropped", dict(B=23, N=3, Tv=515, T=21, Hq=8, Hkv=2, D=64, n_masked=(0, 2)), 64),
 ])
