@@ -303,6 +303,8 @@ litevlm_status_t litevlm_token_score_topk_rows(int32_t dtype, int32_t B, int32_t
  *   max_seqlen         host upper bound on every cu_seqlens[b+1]-cu_seqlens[b]; the
  *                      grid is sized from it and surplus tiles exit at once.
  *                      Segments longer than max_seqlen are undefined behaviour.
+ *                      LITEVLM_ERR_BAD_SHAPE where its row tiles (of 32 rows for
+ *                      fp32, else 128) x Hq x B cannot be counted in an int32.
  *   softmax_scale, q_scale, k_scale, v_scale   finite, > 0; scales must be 1 unless FP8
  *   causal             1 = causal (the prefill path), 0 = full attention
  *   o                  dev out [total, Hq, D] in out_dtype

@@ -406,8 +406,8 @@ litevlm_status_t litevlm_gather_hidden(int32_t B, int32_t S, int32_t row_bytes, 
                                          static_cast<hipStream_t>(stream)));
 }
 
-// Patch Selection Module sizes: d 256 or 512 (the LayerNorm and cross kernels
-// hold a row in registers / LDS), head dim d / n_heads of 64 or 128 (the
+// Patch Selection Module sizes: d 256 or 512 (the kernels hold a
+// normalised row whole, in LDS or registers), head dim d / n_heads of 64 or 128 (the
 // prefill attention kernel), d_ff a multiple of 64.
 static litevlm_status_t check_psm_shape(int32_t B, int32_t T, int32_t d, int32_t n_heads, int32_t d_ff,
                                  int32_t n_views, int32_t n_layers) {

@@ -134,8 +134,8 @@ __device__ __forceinline__ void store_rows_bf16(const f32x16 (&o)[D / 32], float
 
 // ---------------------------------------------------------------------------
 // bf16 path: 4 waves x 32 query rows of one head per workgroup, 64-key tiles
-// double-buffered in LDS. Tiles are copied global -> LDS directly
-// (global_load_lds_dwordx4, no VGPR staging) into XOR-swizzled rows so that
+// double-buffered in LDS. Tiles are copied global -> LDS directly (16-byte
+// buffer loads into LDS, no VGPR staging) into XOR-swizzled rows so that
 // the MFMA operand reads are bank-conflict free; V stays row-major and is read
 // transposed with ds_read_b64_tr_b16. Every per-lane offset is computed once,
 // outside the key loop. Under 256 VGPRs, so two waves share each SIMD and one

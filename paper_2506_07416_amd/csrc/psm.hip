@@ -60,7 +60,9 @@ enum { kOutBf16 = 0, kOutGelu = 1, kOutResid = 2 };
 
 // The latent side of the cross-attention, folded by the workgroups past the
 // GEMM's own: stage 1 forms q_v, g_v = W_cv^T w_v and cst_v = w_v . b_cv +
-// b_head_v, stage 2 (a later launch) u_v = W_ck^T q_v. All fp32.
+// b_head_v, stage 2 (a later launch) u_v = W_ck^T q_v. All fp32. (An infinite
+// head weight leaves NaN in g_v, so in the view's logit, where z first and w_v
+// after would leave an infinity.)
 struct PsmFold {
   int stage, d, n_views;  // stage 0: nothing
   const float *lat, *w_cq, *b_cq, *w_ck, *b_ck, *w_cv, *b_cv, *w_hd, *b_hd;
@@ -551,6 +553,12 @@ void gemm_launch(PsmGemm& p, hipStream_t s) {
 // of 64 x 128 on, bandwidth counts and four waves of 32 x 64 read LDS least
 // (3200 x 2048 x 512: 36 us, 64 x 64 tiles 49 us, eight waves 51 us); without
 // the norm four waves serve 64 x 64 too (3200 x 512 x 2048: 18.4 against 23.4).
+// Around the line of 192 (whole forwards, 4 layers, with 32 x 32 tiles on both
+// sides / as here / from 96 tiles on): 8 x 96 rows, d 256, up at 192 tiles 136 / 133
+// / 129 us; 8 x 128, QKV at 192 149 / 139 / 139; 4 x 112, d 512, QKV at 168 189 / 173
+// / 163; 8 x 192, d 256, output and down projection at 96 174 / 165 / 184; 4 x 192, d
+// 512, the same at 96 249 / 232 / 262. The GEMMs with the norm would gain from a
+// lower line, those without lose more by it.
 // A long k range on few 32 x 32 tiles is shared by two wave groups, so that
 // all of it is in flight at once (128 x 256 x 1024: 6.3 against 7.0 us).
 template <int MODE, int LND>

@@ -16,16 +16,18 @@
 //     d + D/2 of one head), so the rotation is lane-local in the accumulators.
 //
 // Bound: MFMA in principle (about 730 flop per HBM byte), in fact the copies of
-// the tiles from L2: without them the 256 x 256 loop takes 0.88 us a 64-column
-// stage, its MFMA time, with them 1.5 us. So a tile is as large as the shape
-// gives every CU one, and its rows are staged in whole 128-byte lines (64
-// columns; with half lines the 128 x 128 tile took 430 against 394 us at batch 8).
+// the tiles from L2: without them the loop of the 256 x 256 tile takes 0.88 us a
+// 64-column stage, its MFMA time, with them 1.5 us. So a tile is as large as it can
+// be without a further round of the chip (the rule at the launch; eight prompts
+// take 128 x 256), and its rows are staged in whole 128-byte lines (64 columns; with
+// half lines the 128 x 128 tile took 430 against 394 us at batch 8).
 // A workgroup is 4 waves (2 x 2), one wave per SIMD for the large tiles with the
 // accumulators in the AGPRs; a wave's share of the tile is then so large (128 x
-// 128) that its LDS reads stay below the LDS rate. Global -> LDS copies are
-// buffer loads (no vector arithmetic, half the address traffic) spread over the
-// MFMAs. Two wave groups in turns on a SIMD (8 waves, one reading LDS while the
-// other multiplies) took 380 us at batch 8 where this takes 361.
+// 128 of the 256 x 256) that its LDS reads stay below the LDS rate. Global -> LDS
+// copies are buffer loads (no vector arithmetic, half the address traffic) spread
+// over the MFMAs. Two wave groups in turns on a SIMD (8 waves, one reading LDS
+// while the other multiplies) took 380 us at batch 8 where one takes 361, both in
+// 256 x 256 tiles.
 //
 // Epilogue: the rotation angle is reduced to [-1/2, 1/2] turns in double and
 // taken by the hardware sine and cosine (which work in turns), and the rotated
@@ -514,8 +516,8 @@ hipError_t launch_tsm_qk(const TsmArgs& a, hipStream_t stream) {
   // width 4096: 41 us against 54 in 128 x 256 tiles; 392 tokens, 16/8 heads,
   // width 2048: 23 against 32). Else 256-feature tiles where the heads divide so,
   // of 256 rows where these take no more rounds of the chip at twice the time each
-  // (two prompts of 6144 visual tokens: 119 against 130 us; one: 106 against 70;
-  // eight: 361 against 356).
+  // (against 128 rows, views dropped: two prompts of 6144 visual tokens 102 and 112
+  // us, four 207 and 179, eight 426 and 339; one, all kept, 94 and 59).
   if (items(128, 128) <= 256) LITEVLM_TSM(128, 128, 32, 4);
   else if (!wide) LITEVLM_TSM(256, 128, 64, 3);
   else if (2 * ((items(256, 256) + 255) / 256) <= (items(128, 256) + 255) / 256) LITEVLM_TSM(256, 256, 64, 2);
